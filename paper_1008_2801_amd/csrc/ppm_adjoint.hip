@@ -123,7 +123,7 @@ __device__ __forceinline__ void r3_state(const S* w, long long LE, long long off
   for (int m = 0; m < 5; ++m) {
     const S* fa = w + (E_F2 + p12 * 5 + m) * LE + off;
     const S* fb = w + (E_F2 + p21 * 5 + m) * LE + off;
-    ue[m] = ue[m] - c1 * (fa[s1] - fa[0]) - c2 * (fb[s2] - fb[0]);
+    ue[m] = nmadd(c2, fb[s2] - fb[0], nmadd(c1, fa[s1] - fa[0], ue[m]));
   }
 }
 
@@ -350,8 +350,8 @@ __device__ __forceinline__ void adj_r2_pair(const S* __restrict__ w, S* __restri
   for (int m = 0; m < 5; ++m) {
     const S* fL = w + (E_F1 + t * 5 + m) * LE - sd;
     const S* fR = w + (E_F1 + t * 5 + m) * LE;
-    ueL[m] = ue0L[m] - c3 * (fL[stt] - fL[0]);
-    ueR[m] = ue0R[m] - c3 * (fR[stt] - fR[0]);
+    ueL[m] = nmadd(c3, fL[stt] - fL[0], ue0L[m]);
+    ueR[m] = nmadd(c3, fR[stt] - fR[0], ue0R[m]);
   }
   cons_to_prim_dec(ueL, G, L, rfL, pfL);
   cons_to_prim_dec(ueR, G, R, rfR, pfR);

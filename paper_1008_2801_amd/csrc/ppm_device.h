@@ -77,6 +77,7 @@ inline Gas<S> make_gas(double gamma, double small_dens, double small_pres, int l
   G.gm1 = S(gamma - 1.0);
   G.gm1inv = S(1.0 / (gamma - 1.0));
   G.beta = S((gamma + 1.0) / (2.0 * gamma));
+  G.ombeta = S((gamma - 1.0) / (2.0 * gamma));
   G.small_dens = S(small_dens);
   G.small_pres = S(small_pres);
   G.ismall_dens = S(1.0 / small_dens);

@@ -518,8 +518,8 @@ __device__ __forceinline__ void riemann2_pair(const S* __restrict__ w, S* __rest
   for (int m = 0; m < 5; ++m) {
     const S* fL = w + (E_F1 + t * 5 + m) * LE - sd;
     const S* fR = w + (E_F1 + t * 5 + m) * LE;
-    ueL[m] = ueL[m] - c3 * (fL[stt] - fL[0]);
-    ueR[m] = ueR[m] - c3 * (fR[stt] - fR[0]);
+    ueL[m] = nmadd(c3, fL[stt] - fL[0], ueL[m]);
+    ueR[m] = nmadd(c3, fR[stt] - fR[0], ueR[m]);
   }
   cons_to_prim_floor(ueL, G, L, fl);
   cons_to_prim_floor(ueR, G, R, fl);
@@ -597,7 +597,7 @@ __device__ __forceinline__ void riemann3_face(const DevBox& B, const int x[3], c
     for (int m = 0; m < 5; ++m) {
       const S* fa = w + (E_F2 + p12 * 5 + m) * LE + off;
       const S* fb = w + (E_F2 + p21 * 5 + m) * LE + off;
-      ue[m] = ue[m] - c1 * (fa[s1] - fa[0]) - c2 * (fb[s2] - fb[0]);
+      ue[m] = nmadd(c2, fb[s2] - fb[0], nmadd(c1, fa[s1] - fa[0], ue[m]));
     }
     cons_to_prim_floor(ue, G, side == 0 ? L : R, fl);
   }

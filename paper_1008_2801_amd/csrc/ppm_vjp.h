@@ -55,27 +55,26 @@ PPM_HD void flux_vjp(const S g[5], const Gas<S>& G, const S Fb[5], S gb[5]) {
 template <class S>
 PPM_HD void sample_side_vjp(S ro, S uo, S po, S C, S W, S iW, S us, S p, const Gas<S>& G, S rb_, S ub_,
                             S pb_, S& rob, S& uob, S& pob, S& Cb, S& iWb, S& usb, S& pb) {
-  const S irho = qdiv(ONE, ro);
-  const S vstar = irho - (p - po) * (iW * iW);
-  S rs = qdiv(ONE, vstar), ivs = vstar;
+  const S irho = recip(ro);
+  const S vstar = nmadd(p - po, iW * iW, irho);
+  S rs = recip(vstar), ivs = vstar;
   bool fl = false;
   if (!(vstar > S(0)) || rs < G.small_dens) { fl = true; rs = G.small_dens; ivs = G.ismall_dens; }
   const S cst = sqrt_phys(G.gamma * p * ivs);
-  const S co = C * irho;
   S rsb = S(0), cstb = S(0), cob = S(0), irhob = S(0), ivsb = S(0);
   if (p > po) {
-    const S sh = uo - W * irho;
+    const S sh = nmadd(W, irho, uo);
     if (!(sh >= S(0))) { rsb += rb_; usb += ub_; pb += pb_; }
     else { rob += rb_; uob += ub_; pob += pb_; }
   } else {
-    const S hd = uo - co, tl = us - cst;
+    const S hd = nmadd(C, irho, uo), tl = us - cst;
     if (hd >= S(0)) {
       rob += rb_; uob += ub_; pob += pb_;
     } else if (tl <= S(0)) {
       rsb += rb_; usb += ub_; pb += pb_;
     } else {
       const S D = tl - hd;
-      const S iD = qdiv(ONE, D);
+      const S iD = recip(D);
       const S w = -hd * iD;
       const S wb = rb_ * (rs - ro) + ub_ * (us - uo) + pb_ * (p - po);
       rob += (ONE - w) * rb_;
@@ -113,7 +112,7 @@ PPM_HD void sample_side_vjp(S ro, S uo, S po, S C, S W, S iW, S us, S p, const G
 // (the reverse of such a step recomputes its forward from that pressure).
 constexpr int RIEM_KEEP = 3;
 
-// One Newton step of the two-shock iteration, forward (returns the new p).
+// One FP32 Newton step of the two-shock iteration, forward (returns the new p).
 template <class S>
 PPM_HD S riem_iter(S p, S cl, S cr, S pl, S pr, S ul, S ur, S ipl, S ipr, const Gas<S>& G) {
   const S wl = cl * sqrt_wave(ONE + G.beta * (p * ipl - ONE));
@@ -213,13 +212,77 @@ PPM_HD S riem_iter_vjp(S p, S cl, S cr, S pl, S pr, S ul, S ur, S ipl, S ipr, co
   return riem_iter_vjp_rec(r, cl, cr, pl, pr, ul, ur, ipl, ipr, G, pnb, clb, crb, plb, prb, ulb, urb, iplb, iprb);
 }
 
-// Reverse of riemann<d>: Fb = adjoint of the flux; accumulates Lb, Rb.
-// REC: keep each kept Newton step's full record in registers (no forward
-// recomputation in the reverse sweep, more registers) instead of its input
-// pressure alone.
-template <int d, bool REC = false, class S>
-PPM_HD void riemann_vjp(const S L[5], const S R[5], const Gas<S>& G, const S Fb[5], S Lb[5], S Rb[5]) {
+// The star region's part of the reverse of riemann<d>: the flux adjoint
+// through the sampled state.  From the forward values (side speeds C, W,
+// 1/W, star velocity us and pressure p) to the adjoints of both sides'
+// states (Lb, Rb: transverse velocities, accumulated; rlb .. prb), speeds
+// (clb, iwlb, crb, iwrb), us and p (accumulated).
+template <int d, class S>
+PPM_HD void sample_vjp(const S L[5], const S R[5], const Gas<S>& G, const S Fb[5], S cl, S cr, S wl, S wr, S iwl,
+                       S iwr, S us, S pst, S Lb[5], S Rb[5], S& rlb, S& ulb, S& plb, S& clb, S& iwlb, S& rrb,
+                       S& urb, S& prb, S& crb, S& iwrb, S& usb, S& pstb) {
   constexpr int t1 = (d == 0) ? 1 : 0, t2 = (d == 2) ? 1 : 2;
+  const S rl = L[0], ul = L[1 + d], pl = L[4];
+  const S rr = R[0], ur = R[1 + d], pr = R[4];
+  // forward sample -> Godunov state g, then the flux adjoint
+  S g[5];
+  int dummy = 0;
+  if (us != S(0)) {
+    const bool left = us > S(0);
+    S r_, u_, p_;
+    if (left) sample_side(rl, ul, pl, cl, wl, iwl, us, pst, G, r_, u_, p_, dummy);
+    else sample_side(rr, -ur, pr, cr, wr, iwr, -us, pst, G, r_, u_, p_, dummy);
+    g[0] = r_; g[1] = left ? u_ : -u_; g[2] = p_;
+    g[3] = left ? L[1 + t1] : R[1 + t1];
+    g[4] = left ? L[1 + t2] : R[1 + t2];
+  } else {
+    S ra, ua, pa, rb, ub, pb;
+    sample_side(rl, ul, pl, cl, wl, iwl, us, pst, G, ra, ua, pa, dummy);
+    sample_side(rr, -ur, pr, cr, wr, iwr, -us, pst, G, rb, ub, pb, dummy);
+    ub = -ub;
+    g[0] = HALF * (ra + rb); g[1] = HALF * (ua + ub); g[2] = HALF * (pa + pb);
+    g[3] = HALF * (L[1 + t1] + R[1 + t1]);
+    g[4] = HALF * (L[1 + t2] + R[1 + t2]);
+  }
+  S gb[5] = {S(0), S(0), S(0), S(0), S(0)};
+  flux_vjp<d>(g, G, Fb, gb);
+  if (us != S(0)) {
+    // one side sampled: its inputs selected, its adjoints added to that side
+    const bool left = us > S(0);
+    const S sg = left ? ONE : -ONE;
+    S rob = S(0), uob = S(0), pob = S(0), Cb = S(0), iWb = S(0), usbs = S(0);
+    sample_side_vjp(left ? rl : rr, left ? ul : -ur, left ? pl : pr, left ? cl : cr, left ? wl : wr,
+                    left ? iwl : iwr, left ? us : -us, pst, G, gb[0], sg * gb[1], gb[2], rob, uob, pob, Cb, iWb,
+                    usbs, pstb);
+    usb = sg * usbs;
+    // selects, not branches, so that the compiler keeps the adjoints in registers
+    rlb = left ? rob : S(0); ulb = left ? uob : S(0); plb = left ? pob : S(0);
+    clb = left ? Cb : S(0); iwlb = left ? iWb : S(0);
+    rrb = left ? S(0) : rob; urb = left ? S(0) : -uob; prb = left ? S(0) : pob;
+    crb = left ? S(0) : Cb; iwrb = left ? S(0) : iWb;
+    Lb[1 + t1] += left ? gb[3] : S(0);
+    Lb[1 + t2] += left ? gb[4] : S(0);
+    Rb[1 + t1] += left ? S(0) : gb[3];
+    Rb[1 + t2] += left ? S(0) : gb[4];
+  } else {
+    const S h0 = HALF * gb[0], h1 = HALF * gb[1], h2 = HALF * gb[2];
+    sample_side_vjp(rl, ul, pl, cl, wl, iwl, us, pst, G, h0, h1, h2, rlb, ulb, plb, clb, iwlb, usb, pstb);
+    S uob = S(0), usbm = S(0);
+    sample_side_vjp(rr, -ur, pr, cr, wr, iwr, -us, pst, G, h0, -h1, h2, rrb, uob, prb, crb, iwrb, usbm, pstb);
+    urb -= uob;
+    usb -= usbm;
+    Lb[1 + t1] += HALF * gb[3];
+    Rb[1 + t1] += HALF * gb[3];
+    Lb[1 + t2] += HALF * gb[4];
+    Rb[1 + t2] += HALF * gb[4];
+  }
+}
+
+// Reverse of the FP32 solve.
+template <int d, bool REC>
+PPM_HD void riemann_vjp_f32(const float L[5], const float R[5], const Gas<float>& G, const float Fb[5], float Lb[5],
+                            float Rb[5]) {
+  using S = float;
   const S rl = L[0], ul = L[1 + d], pl = L[4];
   const S rr = R[0], ur = R[1 + d], pr = R[4];
   const S cl = sqrt_phys(G.gamma * pl * rl);
@@ -254,62 +317,11 @@ PPM_HD void riemann_vjp(const S L[5], const S R[5], const Gas<S>& G, const S Fb[
   const S NU = (wl * ul + wr * ur) + (pl - pr), DU = wl + wr;
   const S us = qdiv(NU, DU);
 
-  // forward sample -> Godunov state g, then the flux adjoint
-  S g[5];
-  int dummy = 0;
-  if (us != S(0)) {
-    const bool left = us > S(0);
-    S r_, u_, p_;
-    if (left) sample_side(rl, ul, pl, cl, wl, iwl, us, pst, G, r_, u_, p_, dummy);
-    else sample_side(rr, -ur, pr, cr, wr, iwr, -us, pst, G, r_, u_, p_, dummy);
-    g[0] = r_; g[1] = left ? u_ : -u_; g[2] = p_;
-    g[3] = left ? L[1 + t1] : R[1 + t1];
-    g[4] = left ? L[1 + t2] : R[1 + t2];
-  } else {
-    S ra, ua, pa, rb, ub, pb;
-    sample_side(rl, ul, pl, cl, wl, iwl, us, pst, G, ra, ua, pa, dummy);
-    sample_side(rr, -ur, pr, cr, wr, iwr, -us, pst, G, rb, ub, pb, dummy);
-    ub = -ub;
-    g[0] = HALF * (ra + rb); g[1] = HALF * (ua + ub); g[2] = HALF * (pa + pb);
-    g[3] = HALF * (L[1 + t1] + R[1 + t1]);
-    g[4] = HALF * (L[1 + t2] + R[1 + t2]);
-  }
-  S gb[5] = {S(0), S(0), S(0), S(0), S(0)};
-  flux_vjp<d>(g, G, Fb, gb);
-
   S rlb = S(0), ulb = S(0), plb = S(0), clb = S(0), iwlb = S(0);
   S rrb = S(0), urb = S(0), prb = S(0), crb = S(0), iwrb = S(0);
   S usb = S(0), pstb = S(0);
-  if (us != S(0)) {
-    // one side sampled: its inputs selected, its adjoints added to that side
-    const bool left = us > S(0);
-    const S sg = left ? ONE : -ONE;
-    S rob = S(0), uob = S(0), pob = S(0), Cb = S(0), iWb = S(0), usbs = S(0);
-    sample_side_vjp(left ? rl : rr, left ? ul : -ur, left ? pl : pr, left ? cl : cr, left ? wl : wr,
-                    left ? iwl : iwr, left ? us : -us, pst, G, gb[0], sg * gb[1], gb[2], rob, uob, pob, Cb, iWb,
-                    usbs, pstb);
-    usb = sg * usbs;
-    // selects, not branches, so that the compiler keeps the adjoints in registers
-    rlb = left ? rob : S(0); ulb = left ? uob : S(0); plb = left ? pob : S(0);
-    clb = left ? Cb : S(0); iwlb = left ? iWb : S(0);
-    rrb = left ? S(0) : rob; urb = left ? S(0) : -uob; prb = left ? S(0) : pob;
-    crb = left ? S(0) : Cb; iwrb = left ? S(0) : iWb;
-    Lb[1 + t1] += left ? gb[3] : S(0);
-    Lb[1 + t2] += left ? gb[4] : S(0);
-    Rb[1 + t1] += left ? S(0) : gb[3];
-    Rb[1 + t2] += left ? S(0) : gb[4];
-  } else {
-    const S h0 = HALF * gb[0], h1 = HALF * gb[1], h2 = HALF * gb[2];
-    sample_side_vjp(rl, ul, pl, cl, wl, iwl, us, pst, G, h0, h1, h2, rlb, ulb, plb, clb, iwlb, usb, pstb);
-    S uob = S(0), usbm = S(0);
-    sample_side_vjp(rr, -ur, pr, cr, wr, iwr, -us, pst, G, h0, -h1, h2, rrb, uob, prb, crb, iwrb, usbm, pstb);
-    urb -= uob;
-    usb -= usbm;
-    Lb[1 + t1] += HALF * gb[3];
-    Rb[1 + t1] += HALF * gb[3];
-    Lb[1 + t2] += HALF * gb[4];
-    Rb[1 + t2] += HALF * gb[4];
-  }
+  sample_vjp<d>(L, R, G, Fb, cl, cr, wl, wr, iwl, iwr, us, pst, Lb, Rb, rlb, ulb, plb, clb, iwlb, rrb, urb, prb, crb,
+                iwrb, usb, pstb);
   // us = NU / DU
   const S iDU = qdiv(ONE, DU);
   const S NUb = usb * iDU, DUb = -usb * us * iDU;
@@ -371,6 +383,172 @@ PPM_HD void riemann_vjp(const S L[5], const S R[5], const Gas<S>& G, const S Fb[
   Rb[0] += rrb; Rb[1 + d] += urb; Rb[4] += prb;
 }
 
+// What the reverse of one FP64 Newton step needs from its forward
+// evaluation: the input pressure, the two reciprocal roots, and whether the
+// output was bound by the pressure floor.
+struct NewtonRec {
+  double p, yl, yr;
+  bool floored;
+};
+
+PPM_HD double newton_rec(double p, double icl, double icr, double pl, double pr, double ul, double ur, double bipl,
+                         double bipr, const Gas<double>& G, NewtonRec& r) {
+  r.p = p;
+  const double pn = newton_step(p, icl, icr, pl, pr, ul, ur, bipl, bipr, G.ombeta, r.yl, r.yr);
+  r.floored = pn < G.small_pres;
+  return smax(pn, G.small_pres);
+}
+
+// Adjoints that the FP64 solve's reverse sweep accumulates for one side:
+// velocity, pressure, 1/C and beta/p_s.
+struct SideBar {
+  double u, p, ic, bip;
+};
+
+// Reverse of x = 1 - beta + bip p, y = x^(-1/2), iw = ic y for the adjoints
+// iwb of iw and yb of y itself; returns the adjoint of p.
+PPM_HD double wave_vjp(double p, double ic, double bip, double y, double iwb, double yb, SideBar& s) {
+  s.ic = __builtin_fma(iwb, y, s.ic);
+  const double yt = __builtin_fma(iwb, ic, yb);
+  const double xb = -0.5 * yt * (y * y * y);
+  s.bip = __builtin_fma(xb, p, s.bip);
+  return xb * bip;
+}
+
+// Reverse of newton_rec: pnb = adjoint of the output p; returns the adjoint
+// of the input p and accumulates the sides'.
+PPM_HD double newton_vjp(const NewtonRec& r, double icl, double icr, double pl, double pr, double ul, double ur,
+                         double bipl, double bipr, double pnb, SideBar& sl, SideBar& sr) {
+  if (r.floored) return 0.0;  // floor bound: the output does not depend on p
+  const double p = r.p, yl = r.yl, yr = r.yr;
+  const double iwl = icl * yl, iwr = icr * yr;
+  const double tl = __builtin_fma(yl, yl, 1.0), tr = __builtin_fma(yr, yr, 1.0);
+  const double q = iwl * tl + iwr * tr;
+  const double du = __builtin_fma(p - pr, iwr, ur) - __builtin_fma(pl - p, iwl, ul);
+  const double iq = recip(q);
+  const double dub = -2.0 * pnb * iq;
+  const double qb = -dub * du * iq;
+  sl.u -= dub;
+  sr.u += dub;
+  sl.p = __builtin_fma(-dub, iwl, sl.p);
+  sr.p = __builtin_fma(-dub, iwr, sr.p);
+  double pb = __builtin_fma(dub, iwl + iwr, pnb);
+  const double iwlb = __builtin_fma(qb, tl, dub * (p - pl)), iwrb = __builtin_fma(qb, tr, dub * (p - pr));
+  pb += wave_vjp(p, icl, bipl, yl, iwlb, 2.0 * yl * (qb * iwl), sl);
+  pb += wave_vjp(p, icr, bipr, yr, iwrb, 2.0 * yr * (qb * iwr), sr);
+  return pb;
+}
+
+// Reverse of the FP64 solve: the forward values are those of riemann<d>.
+template <int d, bool REC>
+PPM_HD void riemann_vjp_f64(const double L[5], const double R[5], const Gas<double>& G, const double Fb[5],
+                            double Lb[5], double Rb[5]) {
+  using S = double;
+  const S rl = L[0], ul = L[1 + d], pl = L[4];
+  const S rr = R[0], ur = R[1 + d], pr = R[4];
+  S cl, cr, icl, icr;
+  sqrt_pair(G.gamma * pl * rl, cl, icl);
+  sqrt_pair(G.gamma * pr * rr, cr, icr);
+  const S D0 = cl + cr;
+  const S p0r = ((cr * pl + cl * pr) + (cl * cr) * (ul - ur)) * recip(D0);
+  const bool fl0 = p0r < G.small_pres;
+  const S ipl = recip(pl), ipr = recip(pr);
+  const S bipl = G.beta * ipl, bipr = G.beta * ipr;
+  // the first RIEM_KEEP Newton steps' input pressures (with REC their full
+  // records) are kept for the reverse sweep (fully unrolled, so they stay in
+  // registers); later steps are recomputed from the output of the last kept
+  S pin[RIEM_KEEP];
+  NewtonRec rec[REC ? RIEM_KEEP : 1];
+  S pst = smax(p0r, G.small_pres);
+  auto step = [&](S p, NewtonRec& r) { return newton_rec(p, icl, icr, pl, pr, ul, ur, bipl, bipr, G, r); };
+#pragma unroll
+  for (int it = 0; it < RIEM_KEEP; ++it)
+    if (it < G.iters) {
+      NewtonRec r;
+      pin[it] = pst;
+      pst = step(pst, r);
+      if constexpr (REC) rec[it] = r;
+    }
+  const S pkeep = pst;
+  for (int it = RIEM_KEEP; it < G.iters; ++it) {
+    NewtonRec r;
+    pst = step(pst, r);
+  }
+  const S xl = madd(bipl, pst, G.ombeta), xr = madd(bipr, pst, G.ombeta);
+  S gl, gr, yl, yr;
+  sqrt_pair(xl, gl, yl);
+  sqrt_pair(xr, gr, yr);
+  const S wl = cl * gl, wr = cr * gr, iwl = icl * yl, iwr = icr * yr;
+  const S DU = wl + wr;
+  const S us = star_velocity((wl * ul + wr * ur) + (pl - pr), DU);
+
+  S rlb = S(0), ulb = S(0), plb = S(0), clb = S(0), iwlb = S(0);
+  S rrb = S(0), urb = S(0), prb = S(0), crb = S(0), iwrb = S(0);
+  S usb = S(0), pstb = S(0);
+  sample_vjp<d>(L, R, G, Fb, cl, cr, wl, wr, iwl, iwr, us, pst, Lb, Rb, rlb, ulb, plb, clb, iwlb, rrb, urb, prb, crb,
+                iwrb, usb, pstb);
+  // us = NU / DU
+  const S iDU = recip(DU);
+  const S NUb = usb * iDU, DUb = -usb * us * iDU;
+  const S wlb = NUb * ul + DUb, wrb = NUb * ur + DUb;
+  SideBar sl{ulb + NUb * wl, plb + NUb, 0.0, 0.0}, sr{urb + NUb * wr, prb - NUb, 0.0, 0.0};
+  // W = C g, g = x y = x^(1/2): its adjoint enters y's as g' = 1/2 y dx = - x dy
+  clb += wlb * gl;
+  crb += wrb * gr;
+  pstb += wave_vjp(pst, icl, bipl, yl, iwlb, -(wlb * cl) * xl, sl);
+  pstb += wave_vjp(pst, icr, bipr, yr, iwrb, -(wrb * cr) * xr, sr);
+  // Newton iterations in reverse
+  S pb = pstb;
+  auto back = [&](const NewtonRec& r) {
+    pb = newton_vjp(r, icl, icr, pl, pr, ul, ur, bipl, bipr, pb, sl, sr);
+  };
+  for (int k = G.iters - 1; k >= RIEM_KEEP; --k) {
+    NewtonRec r;
+    S pk = pkeep;
+    for (int j = RIEM_KEEP; j < k; ++j) pk = step(pk, r);
+    (void)step(pk, r);
+    back(r);
+  }
+#pragma unroll
+  for (int k = RIEM_KEEP - 1; k >= 0; --k)
+    if (k < G.iters) {
+      if constexpr (REC) {
+        back(rec[k]);
+      } else {
+        NewtonRec r;
+        (void)step(opaque(pin[k]), r);
+        back(r);
+      }
+    }
+  // acoustic guess (floor frozen)
+  if (!fl0) {
+    const S iD0 = recip(D0);
+    const S N0b = pb * iD0, D0b = -N0b * p0r;
+    crb += N0b * (pl + cl * (ul - ur)) + D0b;
+    clb += N0b * (pr + cr * (ul - ur)) + D0b;
+    sl.p += N0b * cr;
+    sr.p += N0b * cl;
+    sl.u += N0b * (cl * cr);
+    sr.u -= N0b * (cl * cr);
+  }
+  sl.p -= G.beta * sl.bip * ipl * ipl;
+  sr.p -= G.beta * sr.bip * ipr * ipr;
+  // ic = 1/c, c^2 = gamma p rho: d c = gamma (rho d p + p d rho) / (2 c)
+  const S hl = (clb - sl.ic * icl * icl) * HALF * G.gamma * icl, hr = (crb - sr.ic * icr * icr) * HALF * G.gamma * icr;
+  Lb[0] += rlb + hl * pl; Lb[1 + d] += sl.u; Lb[4] += sl.p + hl * rl;
+  Rb[0] += rrb + hr * pr; Rb[1 + d] += sr.u; Rb[4] += sr.p + hr * rr;
+}
+
+// Reverse of riemann<d>: Fb = adjoint of the flux; accumulates Lb, Rb.
+// REC: keep each kept Newton step's full record in registers (no forward
+// recomputation in the reverse sweep, more registers) instead of its input
+// pressure alone.
+template <int d, bool REC = false, class S>
+PPM_HD void riemann_vjp(const S L[5], const S R[5], const Gas<S>& G, const S Fb[5], S Lb[5], S Rb[5]) {
+  if constexpr (sizeof(S) == 8) riemann_vjp_f64<d, REC>(L, R, G, Fb, Lb, Rb);
+  else riemann_vjp_f32<d, REC>(L, R, G, Fb, Lb, Rb);
+}
+
 // ----------------------------------------------------------- conversions ---
 // U = cons(q): qb += (dU/dq)^T Ub.
 template <class S>
@@ -401,33 +579,6 @@ PPM_HD void prim_tail_vjp(S r, S u, S v, S w, const Gas<S>& G, S rb, S ub, S vb,
   Ub[3] += wb * ir;
   rb -= (ub * u + vb * v + wb * w) * ir;
   if (!rfloor) Ub[0] += rb;
-}
-
-// q = cons_to_prim_floor(U): Ub += (dq/dU)^T qb.
-template <class S>
-PPM_HD void cons_to_prim_floor_vjp(const S U[5], const Gas<S>& G, const S qb[5], S Ub[5]) {
-  const bool rfl = U[0] < G.small_dens;
-  const S r = smax(U[0], G.small_dens);
-  const S ir0 = qdiv(ONE, r);
-  const S u = U[1] * ir0, v = U[2] * ir0, w = U[3] * ir0;
-  const S ke = HALF * r * ((u * u + v * v) + w * w);
-  const S p = G.gm1 * (U[4] - ke);
-  const S pb = (p < G.small_pres) ? S(0) : qb[4];
-  prim_tail_vjp(r, u, v, w, G, qb[0], qb[1], qb[2], qb[3], pb, Ub, rfl);
-}
-
-// cons_to_prim_floor (same arithmetic), also returning its two floor
-// decisions for the reverse.
-template <class S>
-PPM_HD void cons_to_prim_dec(const S U[5], const Gas<S>& G, S q[5], bool& rfl, bool& pfl) {
-  rfl = U[0] < G.small_dens;
-  const S r = smax(U[0], G.small_dens);
-  const S ir = qdiv(ONE, r);
-  const S u = U[1] * ir, v = U[2] * ir, w = U[3] * ir;
-  const S ke = HALF * r * ((u * u + v * v) + w * w);
-  const S p = G.gm1 * (U[4] - ke);
-  pfl = p < G.small_pres;
-  q[0] = r; q[1] = u; q[2] = v; q[3] = w; q[4] = smax(p, G.small_pres);
 }
 
 // Reverse of cons_to_prim_floor from its outputs q and floor decisions.
@@ -496,11 +647,7 @@ PPM_HD void ppm_parabola_vjp(const S a[5], S phi, const Gas<S>& G, S aLb, S aRb,
   const S aL = HALF * (a[1] + a0) - (s0 - sm) * SIXTH;
   const S aR = HALF * (a0 + a[3]) - (sp - s0) * SIXTH;
   S aL1 = aL, aR1 = aR;
-  if (G.limiter && G.flattening) {
-    const S omp = ONE - phi;
-    aL1 = phi * aL + omp * a0;
-    aR1 = phi * aR + omp * a0;
-  }
+  if (G.limiter && phi != ONE) flatten_edges(a0, phi, aL1, aR1);
   // a6 = 6 a0 - 3 (aL2 + aR2)
   S aL2b = aLb - THREE * a6b, aR2b = aRb - THREE * a6b;
   ab[2] += SIX * a6b;
@@ -588,7 +735,7 @@ PPM_HD void trace_zone_vjp(const S aL[5], const S aR[5], const S a6[5], S r, S u
   S da[5], dab[5];
 #pragma unroll
   for (int i = 0; i < 3; ++i) { da[fm[i]] = aR[fm[i]] - aL[fm[i]]; dab[fm[i]] = S(0); }
-  const S rc = r * c, c2 = c * c, ic2 = qdiv(ONE, c2), hic2 = HALF * ic2, cor = qdiv(c, r);
+  const S rc = r * c, c2 = c * c, ic2 = recip(c2), hic2 = HALF * ic2, cor = qdiv(c, r);
   const S lam[3] = {un - c, un, un + c};
   const S zero = S(0);
   S rcb = zero, c2b = zero, ic2b = zero, hic2b = zero, corb = zero;
@@ -608,9 +755,12 @@ PPM_HD void trace_zone_vjp(const S aL[5], const S aR[5], const S a6[5], S r, S u
     };
     S ref[5];
     for (int i = 0; i < 3; ++i) ref[fm[i]] = I(fm[i], kref);
-    const bool b1 = hi ? (lam[0] > zero) : (lam[0] < zero);
+    // the reference wave's own part is zero (its sweep is the reference) and
+    // so are its derivatives; FP32 still forms them, term by term
+    constexpr bool own = sizeof(S) == 4;
+    const bool b1 = hi ? (lam[0] > zero) : (own && lam[0] < zero);
     const bool b2 = hi ? (lam[1] > zero) : (lam[1] < zero);
-    const bool b3 = hi ? (lam[2] > zero) : (lam[2] < zero);
+    const bool b3 = hi ? (own && lam[2] > zero) : (lam[2] < zero);
     S a1 = zero, a2 = zero, a3 = zero;
     S dp1 = zero, du1 = zero, dr2 = zero, dp2 = zero, dp3 = zero, du3 = zero;
     if (b1) { dp1 = ref[4] - I(4, 0); du1 = ref[mn] - I(mn, 0); a1 = (dp1 - rc * du1) * hic2; }
