@@ -402,11 +402,11 @@ int ppm_get_stream_tiling(const ppm_ctx* ctx, int32_t* sx, int32_t* sy, int32_t*
  * form 2: the x axis's tracing and solves in one kernel whose wavefronts
  * each trace 64 consecutive zones, the first of them the previous
  * wavefront's last, so both states of every x face they solve meet in
- * neighbouring lanes (a lane shuffle; no LDS, no barrier); y and z staged
- * (the default).
- * form 3: the same for every axis; along y and z each wavefront traces an
- * 8 x 8 patch of the x-y or x-z plane whose first row along the axis is the
- * previous patch's last (one zone in eight traced twice).
+ * neighbouring lanes (a lane shuffle; no LDS, no barrier); y and z as in
+ * form 3 on levels large enough for it to pay, else staged (the default).
+ * form 3: every axis fused; along y and z each lane walks a column of traced
+ * zones along the axis with the reconstruction's stencil in registers and
+ * solves each zone's low face from the state carried from the zone below.
  * Results are identical bit for bit in all forms (also for the adjoint's
  * recompute and the species step, which run the same front end).  Tiles of
  * form 1: ppm_set_front_tiling.  The autotuner picks the form and the

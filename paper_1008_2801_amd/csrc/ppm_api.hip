@@ -344,6 +344,16 @@ void add_tiles(std::vector<Tile>& out, int b, int e0, int e1, int e2, int tile, 
   }
 }
 
+// Columns of one box's traced grid along an axis of e slots: COL_THREADS
+// columns per workgroup, the axis cut into equal runs of at most COL_RUN.
+void add_columns(std::vector<Column>& out, int b, int ncol, int e) {
+  const int k = (e + COL_RUN - 1) / COL_RUN;
+  for (int p = 0; p < k; ++p)
+    for (int c = 0; c < ncol; c += COL_THREADS)
+      out.push_back(Column{b, c, std::min(c + COL_THREADS, ncol), (int)((long long)e * p / k),
+                           (int)((long long)e * (p + 1) / k)});
+}
+
 }  // namespace
 
 struct ppm_graph {
@@ -426,7 +436,7 @@ void build_front(ppm_ctx& c) {
 
 // The whole level's ranges of the fused front end's work lists.
 FrontRanges front_all(const ppm_ctx& c) {
-  return FrontRanges{0, (int)c.tilesX.size(), 0, (int)c.tilesY.size(), 0, (int)c.tilesZ.size()};
+  return FrontRanges{0, (int)c.tilesX.size(), 0, (int)c.colsY.size(), 0, (int)c.colsZ.size()};
 }
 
 void build_tiles(ppm_ctx& c) {
@@ -437,9 +447,9 @@ void build_tiles(ppm_ctx& c) {
   c.tilesX.clear();
   c.tilesXA.clear();
   c.tX_begin.assign(1, 0);
-  c.tilesY.clear();
+  c.colsY.clear();
   c.tY_begin.assign(1, 0);
-  c.tilesZ.clear();
+  c.colsZ.clear();
   c.tZ_begin.assign(1, 0);
   for (int b = 0; b < c.layout.nbox; ++b) {
     int n[3];
@@ -448,16 +458,13 @@ void build_tiles(ppm_ctx& c) {
     add_tiles(c.tilesE, b, n[0] + 2, n[1] + 2, n[2] + 2, c.tile, c.strip_rows);
     add_tiles(c.tilesX, b, n[0] + 2, n[1] + 2, n[2] + 2, XF_OWNED, c.strip_rows);
     add_tiles(c.tilesXA, b, n[0] + 2, n[1] + 2, n[2] + 2, XF_OWNED - 1, c.strip_rows);
-    // front form 3: workgroup w of a box along y or z; the kernel decodes w
-    for (long long w = 0; w < front_yz_groups(n[0] + 2, n[1] + 2, n[2] + 2); ++w)
-      c.tilesY.push_back(Tile{b, (int)w, (int)w + 1});
-    for (long long w = 0; w < front_yz_groups(n[0] + 2, n[2] + 2, n[1] + 2); ++w)
-      c.tilesZ.push_back(Tile{b, (int)w, (int)w + 1});
+    add_columns(c.colsY, b, (n[0] + 2) * (n[2] + 2), n[1] + 2);
+    add_columns(c.colsZ, b, (n[0] + 2) * (n[1] + 2), n[2] + 2);
     c.tS_begin.push_back((int)c.tilesS.size());
     c.tE_begin.push_back((int)c.tilesE.size());
     c.tX_begin.push_back((int)c.tilesX.size());
-    c.tY_begin.push_back((int)c.tilesY.size());
-    c.tZ_begin.push_back((int)c.tilesZ.size());
+    c.tY_begin.push_back((int)c.colsY.size());
+    c.tZ_begin.push_back((int)c.colsZ.size());
   }
 }
 
@@ -640,8 +647,8 @@ int ppm_ctx_create(const ppm_layout* layout, ppm_ctx** out) {
       (e = upload(&ctx->d_tilesE, ctx->tilesE)) != hipSuccess ||
       (e = upload(&ctx->d_tilesX, ctx->tilesX)) != hipSuccess ||
       (e = upload(&ctx->d_tilesXA, ctx->tilesXA)) != hipSuccess ||
-      (e = upload(&ctx->d_tilesY, ctx->tilesY)) != hipSuccess ||
-      (e = upload(&ctx->d_tilesZ, ctx->tilesZ)) != hipSuccess ||
+      (e = upload(&ctx->d_colsY, ctx->colsY)) != hipSuccess ||
+      (e = upload(&ctx->d_colsZ, ctx->colsZ)) != hipSuccess ||
       (e = upload(&ctx->d_desc, ctx->plan->desc)) != hipSuccess ||
       (e = upload(&ctx->d_start, ctx->plan->start)) != hipSuccess ||
       (e = hipMalloc((void**)&ctx->d_consts, sizeof(StepConsts))) != hipSuccess ||
@@ -669,8 +676,8 @@ int ppm_ctx_destroy(ppm_ctx* ctx) {
   (void)hipFree(ctx->d_tilesE);
   (void)hipFree(ctx->d_tilesX);
   (void)hipFree(ctx->d_tilesXA);
-  (void)hipFree(ctx->d_tilesY);
-  (void)hipFree(ctx->d_tilesZ);
+  (void)hipFree(ctx->d_colsY);
+  (void)hipFree(ctx->d_colsZ);
   (void)hipFree(ctx->d_bricks);
   (void)hipFree(ctx->d_fbricks);
   (void)hipFree(ctx->d_desc);
@@ -1168,18 +1175,18 @@ int ppm_set_tiling(ppm_ctx* ctx, int32_t tile, int32_t strip_rows) {
   (void)hipFree(ctx->d_tilesE);
   (void)hipFree(ctx->d_tilesX);
   (void)hipFree(ctx->d_tilesXA);
-  (void)hipFree(ctx->d_tilesY);
-  (void)hipFree(ctx->d_tilesZ);
+  (void)hipFree(ctx->d_colsY);
+  (void)hipFree(ctx->d_colsZ);
   ctx->d_tilesS = nullptr;
   ctx->d_tilesE = nullptr;
   ctx->d_tilesX = nullptr;
   ctx->d_tilesXA = nullptr;
-  ctx->d_tilesY = nullptr;
-  ctx->d_tilesZ = nullptr;
+  ctx->d_colsY = nullptr;
+  ctx->d_colsZ = nullptr;
   if ((e = upload(&ctx->d_tilesS, ctx->tilesS)) != hipSuccess || (e = upload(&ctx->d_tilesE, ctx->tilesE)) != hipSuccess ||
       (e = upload(&ctx->d_tilesX, ctx->tilesX)) != hipSuccess ||
-      (e = upload(&ctx->d_tilesXA, ctx->tilesXA)) != hipSuccess || (e = upload(&ctx->d_tilesY, ctx->tilesY)) != hipSuccess ||
-      (e = upload(&ctx->d_tilesZ, ctx->tilesZ)) != hipSuccess)
+      (e = upload(&ctx->d_tilesXA, ctx->tilesXA)) != hipSuccess || (e = upload(&ctx->d_colsY, ctx->colsY)) != hipSuccess ||
+      (e = upload(&ctx->d_colsZ, ctx->colsZ)) != hipSuccess)
     return ctx->hip(e, "tiling upload");
   return PPM_OK;
 }

@@ -39,7 +39,7 @@ struct ppm_ctx {
   std::vector<Tile> tilesX;             // front forms 2, 3: traced-grid runs of XF_OWNED zones
   std::vector<Tile> tilesXA;            // adjoint along x: traced-grid runs of XF_OWNED - 1 zones
   std::vector<int> tX_begin;            // nbox + 1
-  std::vector<Tile> tilesY, tilesZ;     // front form 3: 8 x 8 wavefront patches (x-d planes) along y, z
+  std::vector<Column> colsY, colsZ;     // front forms 2, 3: columns along y, z
   std::vector<int> tY_begin, tZ_begin;  // nbox + 1
   std::vector<Brick> bricks;
   std::vector<int> tB_begin;            // nbox + 1
@@ -48,8 +48,8 @@ struct ppm_ctx {
   // front end: 0 trace and stage-1 solves as two staged kernels; 1 one
   // kernel streamed along z over x-y tiles of the traced grids (fbricks,
   // at most front_e zones per axis, balanced per box); 2 the x axis's trace
-  // and solves in one kernel (tilesX), y and z staged; 3 each axis's trace
-  // and solves in one kernel (tilesX, tilesY, tilesZ)
+  // and solves in one kernel (tilesX), y's and z's in columns (colsY, colsZ)
+  // where that pays, else staged; 3 in columns always
   int front = 2;
   int front_e[3] = {16, 8, 32};
   std::vector<Brick> fbricks;
@@ -69,8 +69,8 @@ struct ppm_ctx {
   Tile* d_tilesE = nullptr;
   Tile* d_tilesX = nullptr;
   Tile* d_tilesXA = nullptr;
-  Tile* d_tilesY = nullptr;
-  Tile* d_tilesZ = nullptr;
+  Column* d_colsY = nullptr;
+  Column* d_colsZ = nullptr;
   Brick* d_bricks = nullptr;
   Brick* d_fbricks = nullptr;
   FillDesc* d_desc = nullptr;
@@ -117,8 +117,8 @@ struct ppm_ctx {
     L.tilesE = d_tilesE;
     L.tilesX = d_tilesX;
     L.tilesXA = d_tilesXA;
-    L.tilesY = d_tilesY;
-    L.tilesZ = d_tilesZ;
+    L.colsY = d_colsY;
+    L.colsZ = d_colsZ;
     L.desc = d_desc;
     L.desc_start = d_start;
     L.consts = d_consts;

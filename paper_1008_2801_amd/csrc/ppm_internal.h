@@ -71,12 +71,15 @@ constexpr int FRONT_MAX_THREADS = 512;
 // last (so every x face's two states meet in one wavefront)
 constexpr int XF_THREADS = 256;
 constexpr int XF_OWNED = XF_THREADS / 64 * 63;
-// front form 3 along y and z: each wavefront an 8 x 8 patch (8 x slots, 8
-// slots along the axis, the first a halo), a workgroup 4 patches side by
-// side in x; workgroups per box: ceil(E0 / 32) x ceil(E_d / 7) x E_other
-inline long long front_yz_groups(int E0, int Ed, int Eo) {
-  return (long long)((E0 + 31) / 32) * ((Ed + 6) / 7) * Eo;
-}
+// columns of the fused front end along y and z: a workgroup's lanes take the
+// columns [c0, c1) (x slots fastest, then the third axis) and walk the slots
+// [k0, k1) of the axis
+constexpr int COL_THREADS = 256;
+constexpr int COL_RUN = 16;  // slots per run (8 and 32: 3% and 1% slower on 256^3 FP64)
+struct Column {
+  int box;
+  int c0, c1, k0, k1;
+};
 // ranges of the front forms' work lists of a launch
 struct FrontRanges {
   int x0, x1, y0, y1, z0, z1;
@@ -158,8 +161,8 @@ struct DevLevel {
   const Tile* tilesE;  // tiles over the traced grids
   const Tile* tilesX;  // runs of XF_OWNED traced zones (front forms 2, 3)
   const Tile* tilesXA;  // runs of XF_OWNED - 1 traced zones (adjoint along x)
-  const Tile* tilesY;  // workgroups of 8 x 8 patches in x-y planes (front form 3)
-  const Tile* tilesZ;  // workgroups of 8 x 8 patches in x-z planes (front form 3)
+  const Column* colsY;  // columns along y and z (front forms 2, 3)
+  const Column* colsZ;
   const FillDesc* desc;
   const long long* desc_start;  // exclusive prefix of zone counts, ndesc+1
   StepConsts* consts;
@@ -175,8 +178,8 @@ struct DevLevel {
   int stream_e[3];      // form 2: x, y extents of a tile (threads = product) and the z run
   const Brick* fbricks; // traced-grid x-y tiles with z runs (streamed front end)
   int front;            // 1: trace + stage-1 solves in one kernel streamed along z (k_front_stream);
-                        // 2: the x axis's trace + stage-1 solves in one kernel (k_front_x);
-                        // 3: every axis's (k_front_x, k_front_yz)
+                        // 2: the x axis's trace + stage-1 solves in one kernel (k_front_x), y's and z's
+                        // in columns where that pays (k_front_yz); 3: in columns always
   int front_m[2];       // largest x, y extents of the front tiles (LDS layout, lanes)
 };
 

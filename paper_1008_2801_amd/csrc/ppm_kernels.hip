@@ -15,8 +15,8 @@
 //
 // Fused forms of some stage pairs cut that traffic and give the same bits:
 // the front end (trace + riemann1) along x with the face states exchanged
-// by lane shuffles (k_front_x, the default), also along y and z
-// (k_front_yz), or streamed along z through LDS (k_front_stream); the final
+// by lane shuffles (k_front_x, the default), along y and z in columns with the
+// stencil in registers (k_front_yz, the default on large levels), or streamed along z through LDS (k_front_stream); the final
 // stage (riemann3 + update) in bricks (k_final_update) or streamed along z
 // (k_final_stream), the final fluxes kept in LDS.
 //
@@ -171,8 +171,20 @@ __global__ void __launch_bounds__(MAX_TILE) k_flatten(const Tile* __restrict__ t
   flatten_body(xcd_tile(ntiles), tiles, boxes, prim, LS, work, LE, G);
 }
 
-// O4 + O5 along axis d for zone (x, y, z) of box B (e: its index in the
-// traced grid): the states at the zone's high (qp) and low (qm) d faces.
+// O4 + O5 along axis d from a zone's stencil values v[m][o] (field m at offset
+// o - 2 along d) and flattening coefficient: the states at the zone's high (qp)
+// and low (qm) d faces.
+template <int d, class S>
+__device__ __forceinline__ void trace_vals(const S v[5][5], S phi, const Gas<S>& G, const StepConsts* __restrict__ sc,
+                                           S qp[5], S qm[5], int& fl) {
+  const S c = sound_speed(v[0][2], v[4][2], G);
+  S aL[5], aR[5], a6[5];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) ppm_parabola(v[m][0], v[m][1], v[m][2], v[m][3], v[m][4], phi, G, aL[m], aR[m], a6[m]);
+  trace_zone<d>(aL, aR, a6, v[0][2], v[1 + d][2], c, SC<S>::dtdx(sc)[d], G, SC<S>::hdtg(sc), qp, qm, fl);
+}
+
+// The same for zone (x, y, z) of box B (e: its index in the traced grid).
 template <int d, class S>
 __device__ __forceinline__ void trace_at(const DevBox& B, int x, int y, int z, long long e,
                                          const S* __restrict__ prim, long long LS, const S* __restrict__ work,
@@ -191,13 +203,7 @@ __device__ __forceinline__ void trace_at(const DevBox& B, int x, int y, int z, l
 #pragma unroll
     for (int o = 0; o < 5; ++o) v[m][o] = a[(o - 2) * st];
   }
-  const S c = sound_speed(v[0][2], v[4][2], G);
-  const S phi = work[E_FLAT * LE + B.eoff + e];
-  S aL[5], aR[5], a6[5];
-#pragma unroll
-  for (int m = 0; m < 5; ++m) ppm_parabola(v[m][0], v[m][1], v[m][2], v[m][3], v[m][4], phi, G, aL[m], aR[m], a6[m]);
-  const S r = v[0][2], un = v[1 + d][2];
-  trace_zone<d>(aL, aR, a6, r, un, c, SC<S>::dtdx(sc)[d], G, SC<S>::hdtg(sc), qp, qm, fl);
+  trace_vals<d>(v, work[E_FLAT * LE + B.eoff + e], G, sc, qp, qm, fl);
 }
 
 // Traced states of zone e along d into the workspace planes.
@@ -340,53 +346,98 @@ __global__ void __launch_bounds__(XF_THREADS) k_front_x(const Tile* __restrict__
   raise_flags(flags, fl);
 }
 
-// O4 + O5 + O7 along d (y or z) in one kernel: each wavefront traces an
-// 8 x 8 patch of the x-d plane (8 consecutive x slots, 8 slots along d, the
-// first of them the previous patch's last: a halo, traced, not stored), so
-// the two states of every d face it solves sit 8 lanes apart and the low
-// side arrives by a lane shuffle.  A workgroup is 4 patches side by side in
-// x at one slot of the third axis; its index w within the box (Tile.start)
-// runs over x first, then the bands of 7 slots along d, then that third
-// axis.  Same arithmetic as trace_at and stage1_face, so the same bits as
+// O4 + O5 + O7 along d (y or z) in one kernel: each lane walks a column of
+// traced zones along d with the stencil of all five fields in registers, so
+// that a zone's primitives are loaded once instead of five times, and solves
+// the stage-1 problem of each zone's low face from the high-face state carried
+// from the zone below, so the traced states are stored (later stages read
+// them) but not read back.  A run's first step traces the zone below the run
+// once more.  Same arithmetic as trace_at and stage1_face, so the same bits as
 // the staged trace and riemann1 kernels along d.
+// The staged trace is bound by the misses a CU can have in flight: it asks L2
+// for 64 M lines per 256^3 launch, a quarter of which hold new data (61 in
+// flight per CU on average, the most any kernel of the step reaches is 89).
+// Here every line is asked for once; 138 registers in FP64 (3 waves per SIMD)
+// are enough.  Measured against trace + riemann1 (y, z): 256^3 FP64 2.06 ->
+// 1.58 ms, FP32 1.13 -> 0.98, 216 boxes of 64^3 7.36 -> 5.66, 512 boxes of 16
+// to 64 zones per edge 2.46 -> 2.17, 128^3 0.305 -> 0.262.
 template <int d, class S>
-__global__ void __launch_bounds__(XF_THREADS) k_front_yz(const Tile* __restrict__ tiles, int ntiles,
-                                                     const DevBox* __restrict__ boxes, const S* __restrict__ prim,
-                                                     long long LS, S* __restrict__ work, long long LE, Gas<S> G,
-                                                     const StepConsts* __restrict__ sc, int* flags) {
-  constexpr int o = 3 - d;  // the third axis
-  const int t = xcd_tile(ntiles);
-  if (t < 0) return;  // the whole workgroup
-  const Tile tl = tiles[t];
-  const DevBox B = boxes[tl.box];
-  const int E[3] = {B.n[0] + 2, B.n[1] + 2, B.n[2] + 2};
-  const int nq = (E[0] + 31) / 32, nb = (E[d] + 6) / 7;
-  const int w = tl.start;
-  const int q = w % nq, band = (w / nq) % nb, so = w / (nq * nb);
-  const int lane = threadIdx.x & 63, i = lane & 7, j = lane >> 3;
-  const int xs = 32 * q + 8 * (int)(threadIdx.x >> 6) + i;  // slots: zone = slot - 1
-  const int ds = 7 * band + j - 1;
-  const bool act = xs < E[0] && ds >= 0 && ds < E[d];
-  const bool own = act && j >= 1;
-  int X[3];
-  X[0] = xs - 1;
-  X[d] = ds - 1;
-  X[o] = so - 1;
-  const long long e = ((long long)(X[2] + 1) * E[1] + (X[1] + 1)) * E[0] + (X[0] + 1);
-  S qp[5], qm[5];
-  int fl = 0;
-  if (act) {
-    trace_at<d>(B, X[0], X[1], X[2], e, prim, LS, work, LE, G, sc, qp, qm, fl);
-    if (own) store_traced<d>(work, LE, B, e, qp, qm);
-  } else {
+__device__ __forceinline__ void front_column(const Column& C, const DevBox* __restrict__ boxes,
+                                             const S* __restrict__ prim, long long LS, S* __restrict__ work,
+                                             long long LE, const Gas<S>& G, const StepConsts* __restrict__ sc,
+                                             int* flags) {
+  const DevBox B = boxes[C.box];
+  const int c = C.c0 + (int)threadIdx.x;
+  if (c >= C.c1) return;
+  // column (x, o): x slots fastest, then the third axis
+  const int q = (int)div31((unsigned)c, B.de[0]);
+  const int E0 = B.n[0] + 2, x = c - q * E0;
+  const int NS[3] = {B.n[0] + 2 * NG, B.n[1] + 2 * NG, B.n[2] + 2 * NG};
+  const long long st = stride(NS, d);
+  const long long se = d == 1 ? E0 : (long long)E0 * (B.n[1] + 2);
+  const int s0 = C.k0 > 0 ? C.k0 - 1 : 0;  // first traced slot (zone s0 - 1)
+  const S* p = prim + (d == 1 ? pidx(B, x - 1, s0 - 1, q - 1) : pidx(B, x - 1, q - 1, s0 - 1));
+  long long e = (d == 1 ? (long long)q * (B.n[1] + 2) * E0 : (long long)q * E0) + s0 * se + x;
+  const S* ph = work + E_FLAT * LE + B.eoff;
+  S v[5][5], L[5], phi = ph[e];
 #pragma unroll
-    for (int m = 0; m < 5; ++m) qp[m] = qm[m] = S(0);
+  for (int m = 0; m < 5; ++m) {
+#pragma unroll
+    for (int o = 0; o < 5; ++o) v[m][o] = p[m * LS + (o - 2) * st];
+    L[m] = S(0);
   }
-  S L[5];
+  int fl = 0;
+  for (int k = s0; k < C.k1; ++k) {
+    S nv[5], nphi = S(0);
+    const bool more = k + 1 < C.k1;  // uniform
+    S qp[5], qm[5];
+    trace_vals<d>(v, phi, G, sc, qp, qm, fl);
+    if (k >= C.k0) {
+      store_traced<d>(work, LE, B, e, qp, qm);
+      if (k > 0) stage1_face<d>(B, k - 1, L, qm, G, work, LE, e, fl);
+    }
+    if (more) {
 #pragma unroll
-  for (int m = 0; m < 5; ++m) L[m] = __shfl_up(qp[m], 8, 64);
-  if (own && X[d] >= 0) stage1_face<d>(B, X[d], L, qm, G, work, LE, e, fl);
+      for (int m = 0; m < 5; ++m) nv[m] = p[m * LS + 3 * st];
+      nphi = ph[e + se];
+    }
+#pragma unroll
+    for (int m = 0; m < 5; ++m) {
+      L[m] = qp[m];
+#pragma unroll
+      for (int o = 0; o < 4; ++o) v[m][o] = v[m][o + 1];
+      v[m][4] = more ? nv[m] : S(0);
+    }
+    phi = nphi;
+    p += st;
+    e += se;
+  }
   raise_flags(flags, fl);
+}
+
+// Columns pay where one pass of trace's planes no longer stays in the 256 MB
+// Infinity Cache, so that reading them back costs HBM traffic (some 30 planes
+// of 8 MB; measured: 96^3 FP64, 7.5 MB planes, 95 us staged against 126 us,
+// 128^3, 17 MB, 305 against 262; 128^3 FP32, 9 MB, 145 against 172), and where
+// the runs fill the card (a workgroup or more for each of its 1024 SIMDs).
+template <class S>
+bool columns_pay(long long LE, int groups) {
+  return LE * (long long)sizeof(S) >= (16ll << 20) && groups >= 1024;
+}
+
+// y columns first (ny of them), then z columns.
+template <class S>
+__global__ void __launch_bounds__(COL_THREADS) k_front_yz(const Column* __restrict__ cy, int ny,
+                                                      const Column* __restrict__ cz, int nz,
+                                                      const DevBox* __restrict__ boxes, const S* __restrict__ prim,
+                                                      long long LS, S* __restrict__ work, long long LE, Gas<S> G,
+                                                      const StepConsts* __restrict__ sc, int* flags) {
+  const int t = xcd_tile(ny + nz);
+  if (t < 0) return;
+  if (t < ny)
+    front_column<1>(cy[t], boxes, prim, LS, work, LE, G, sc, flags);
+  else
+    front_column<2>(cz[t - ny], boxes, prim, LS, work, LE, G, sc, flags);
 }
 
 // O4-O7 fused and streamed along z: a workgroup owns an x-y tile of
@@ -1109,18 +1160,16 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
     if (ev) (void)hipEventRecord(ev[3], s);
     if (ev) (void)hipEventRecord(ev[4], s);
   } else {
-    // front forms 2 and 3: the x axis, or every axis, in one kernel each
-    // (timed in the trace slot); the other axes staged
+    // front forms 2 and 3: the x axis's trace and solves in one kernel, y's and
+    // z's in columns always (3) or where that pays (2) (timed in the trace slot)
     const int nX = fr.x1 - fr.x0, nY = fr.y1 - fr.y0, nZ = fr.z1 - fr.z0;
     const int d0 = (L.front >= 2 && nX > 0) ? 1 : 0;
     if (d0)
       hipLaunchKernelGGL(k_front_x<S>, dim3(xcd_grid(nX)), dim3(XF_THREADS), 0, s, L.tilesX + fr.x0, nX, L.boxes,
                          (const S*)prim, L.LS, ework, L.LE, G, L.consts, L.flags);
-    if (L.front == 3 && d0 && nY > 0 && nZ > 0) {
-      hipLaunchKernelGGL((k_front_yz<1, S>), dim3(xcd_grid(nY)), dim3(XF_THREADS), 0, s, L.tilesY + fr.y0, nY,
-                         L.boxes, (const S*)prim, L.LS, ework, L.LE, G, L.consts, L.flags);
-      hipLaunchKernelGGL((k_front_yz<2, S>), dim3(xcd_grid(nZ)), dim3(XF_THREADS), 0, s, L.tilesZ + fr.z0, nZ,
-                         L.boxes, (const S*)prim, L.LS, ework, L.LE, G, L.consts, L.flags);
+    if (d0 && nY + nZ > 0 && (L.front == 3 || columns_pay<S>(L.LE, nY + nZ))) {
+      hipLaunchKernelGGL(k_front_yz<S>, dim3(xcd_grid(nY + nZ)), dim3(COL_THREADS), 0, s, L.colsY + fr.y0, nY,
+                         L.colsZ + fr.z0, nZ, L.boxes, (const S*)prim, L.LS, ework, L.LE, G, L.consts, L.flags);
       if (ev) (void)hipEventRecord(ev[3], s);
     } else {
       hipLaunchKernelGGL(k_trace<S>, dim3(xcd_grid(nE), 3 - d0), blk, 0, s, TE, nE, L.boxes, prim, L.LS, ework,

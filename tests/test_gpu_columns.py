@@ -1,0 +1,65 @@
+"""Kernels whose lanes walk columns of a box (a stencil or a carried state in
+registers along y or z) against the staged kernels on the same input, bit for
+bit, at box sizes around the run lengths and workgroup sizes of the columns:
+extents of one and two zones, one run, a run and a remainder, more columns
+than one workgroup, several boxes, walls and gravity."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_1008_2801_amd import inputs as I  # noqa: E402
+from paper_1008_2801_amd import ppm as P  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+# per-axis box sizes of a tensor tiling
+TILINGS = [([5], [4], [4]), ([1, 7], [3, 1], [2, 5]), ([17], [14], [15]), ([64], [15, 2], [33]),
+           ([70, 3], [16, 31], [6, 1, 9]), ([4], [40], [4, 18])]
+
+
+def _level(tiling, precision, seed=9):
+    lay = I.tensor_tiling(*tiling, bc=(0, 0, 0, 0, 2, 2))
+    h = (1.0 / 32, 1.0 / 24, 1.0 / 40)
+    rng = np.random.default_rng(seed)
+    S = [I.ModeSum(rng, 6, 4, (1.0, 1.0, 1.0)) for _ in range(5)]
+
+    def prim(x, y, z):
+        left = x < 0.06
+        return (np.where(left, 1.0, 0.3) * (1.0 + 0.3 * S[0](x, y, z)), 0.4 * S[1](x, y, z), 0.4 * S[2](x, y, z),
+                0.4 * S[3](x, y, z), np.where(left, 1.0, 0.2) * (1.0 + 0.3 * S[4](x, y, z)))
+    U = torch.from_numpy(I._fill_state(lay, h, 1.4, prim)).cuda()
+    return lay, h, U, P.params(gamma=1.4, grav=(0.1, 0.0, -0.4), precision=precision)
+
+
+def _step(lay, h, U, p, mode, front, form=0):
+    lev = P.Level(lay)
+    lev.set_front_form(front)
+    lev.set_step_form(form)
+    A = U.clone()
+    lev.fill_boundary(A)
+    B = torch.zeros_like(A)
+    F = lev.new_fluxes()
+    dt = lev.compute_dt(A, h, p)
+    nxt = torch.zeros(2, dtype=torch.float64, device="cuda")
+    lev.hydro_step(A, B, h, p, dt_dev=dt, fluxes=F, mode=mode, dt_next=nxt)
+    # the intermediates the adjoint reads from the step workspace
+    w = torch.ones_like(A)
+    G = torch.zeros_like(A)
+    lev.hydro_step_adjoint(A, w, G, h, p, dt_dev=dt, saved=True)
+    return B, nxt, G, F
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("tiling", TILINGS)
+def test_front_columns_agree_bitwise(tiling, precision):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lay, h, U, p = _level(tiling, precision)
+    for mode in (P.BATCHED, P.PER_BOX):
+        ref = _step(lay, h, U, p, mode, 0)
+        got = _step(lay, h, U, p, mode, 3)
+        for a, b in zip(ref[:3], got[:3]):
+            assert torch.equal(a, b), (tiling, precision, mode)
+        for a, b in zip(ref[3], got[3]):
+            assert torch.equal(a, b), (tiling, precision, mode)
