@@ -100,7 +100,7 @@ constexpr int BRICK_FACES = BRICK_FACES_D(0) > BRICK_FACES_D(1)
 struct Brick {
   int box;
   int o[3], e[3];
-  Div31 d0[2], d1[2];  // division by e_x and e_x + 1, by e_y and e_y + 1
+  Div31 d0[2], d1[2];  // division by e_x and e_x + 1, by e_y and e_y + 1 (extents of 2 or more)
 };
 inline void brick_divisors(Brick& K) {
   for (int k = 0; k < 2; ++k) {

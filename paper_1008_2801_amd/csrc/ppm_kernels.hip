@@ -847,6 +847,10 @@ __global__ void __launch_bounds__(MAX_TILE) k_update(const Tile* __restrict__ ti
 // maximum.  The arithmetic is riemann3_face, update_zone and
 // fold_signal_speed, so the results are those of the staged kernels bit for
 // bit.
+// n / D of a brick's extent D >= 1 (div31's multiplier needs D >= 2; a box one
+// zone longer than whole bricks ends in bricks one zone thin).
+__device__ __forceinline__ unsigned div_extent(unsigned n, int D, Div31 q) { return D == 1 ? n : div31(n, q); }
+
 template <int d, class S>
 __device__ __forceinline__ void brick_faces(const Brick& K, const DevBox& B, const S* __restrict__ work,
                                             long long LE, const Gas<S>& G, const StepConsts* __restrict__ sc,
@@ -855,7 +859,7 @@ __device__ __forceinline__ void brick_faces(const Brick& K, const DevBox& B, con
   ex[d] += 1;
   const int nf = ex[0] * ex[1] * ex[2];
   for (int f = threadIdx.x; f < nf; f += BRICK_THREADS) {
-    const unsigned r = div31((unsigned)f, K.d0[d == 0]), k = div31(r, K.d1[d == 1]);
+    const unsigned r = div_extent((unsigned)f, ex[0], K.d0[d == 0]), k = div_extent(r, ex[1], K.d1[d == 1]);
     const int x[3] = {K.o[0] + f - (int)r * ex[0], K.o[1] + (int)(r - k * (unsigned)ex[1]), K.o[2] + (int)k};
     S F[5];
     riemann3_face<d>(B, x, work, LE, G, sc, F, fl);
@@ -890,7 +894,7 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_final_update(const Brick* __r
   const long long NS = (long long)N0 * N1 * N2;
   double smax_lane = 0.0;
   for (int z = threadIdx.x; z < e0 * e1 * e2; z += BRICK_THREADS) {
-    const unsigned r = div31((unsigned)z, K.d0[0]), k = div31(r, K.d1[0]);
+    const unsigned r = div_extent((unsigned)z, e0, K.d0[0]), k = div_extent(r, e1, K.d1[0]);
     const int l0 = z - (int)r * e0, l1 = (int)(r - k * (unsigned)e1), l2 = (int)k;
     const int ix = (l2 * e1 + l1) * (e0 + 1) + l0;        // x-face below the zone
     const int iy = (l2 * (e1 + 1) + l1) * e0 + l0;        // y-face below

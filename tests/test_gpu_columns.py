@@ -63,3 +63,15 @@ def test_front_columns_agree_bitwise(tiling, precision):
             assert torch.equal(a, b), (tiling, precision, mode)
         for a, b in zip(ref[3], got[3]):
             assert torch.equal(a, b), (tiling, precision, mode)
+
+
+@pytest.mark.parametrize("tiling", [([33], [5], [6]), ([1], [9], [5]), ([65, 2], [1, 4], [1, 3])])
+def test_bricks_one_zone_thin_agree_bitwise(tiling):
+    """Boxes one zone longer than whole bricks (32 x 4 x 4) along x, y or z."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lay, h, U, p = _level(tiling, 0)
+    ref = _step(lay, h, U, p, P.BATCHED, 0)
+    got = _step(lay, h, U, p, P.BATCHED, 0, form=1)
+    for a, b in zip(list(ref[:3]) + list(ref[3]), list(got[:3]) + list(got[3])):
+        assert torch.equal(a, b), tiling
