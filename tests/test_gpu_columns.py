@@ -65,7 +65,7 @@ def test_front_columns_agree_bitwise(tiling, precision):
             assert torch.equal(a, b), (tiling, precision, mode)
 
 
-@pytest.mark.parametrize("tiling", [([33], [5], [6]), ([1], [9], [5]), ([65, 2], [1, 4], [1, 3])])
+@pytest.mark.parametrize("tiling", [([33], [5], [6]), ([4, 1], [9], [5]), ([65, 2], [1, 4], [1, 3])])
 def test_bricks_one_zone_thin_agree_bitwise(tiling):
     """Boxes one zone longer than whole bricks (32 x 4 x 4) along x, y or z."""
     if not torch.cuda.is_available():
