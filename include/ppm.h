@@ -364,7 +364,9 @@ int ppm_set_tiling(ppm_ctx* ctx, int32_t tile, int32_t strip_rows);
 int ppm_get_tiling(const ppm_ctx* ctx, int32_t* tile, int32_t* strip_rows);
 
 /* Form of the step's last stage.  fused = 0 (the default): the final
- * fluxes go to the workspace and a separate kernel updates the zones.
+ * fluxes go to the workspace and a separate kernel updates the zones, or, on
+ * large FP64 levels, one kernel whose lanes walk columns of zones along z does
+ * both, the final fluxes kept in registers.
  * fused = 1: the final fluxes of each brick of 32 x 4 x 4 valid zones are
  * computed into LDS and the brick is updated from them in the same kernel
  * (the fluxes on a brick's faces are computed by both bricks that share

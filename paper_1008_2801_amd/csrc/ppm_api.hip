@@ -345,12 +345,13 @@ void add_tiles(std::vector<Tile>& out, int b, int e0, int e1, int e2, int tile, 
 }
 
 // Columns of one box's traced grid along an axis of e slots: COL_THREADS
-// columns per workgroup, the axis cut into equal runs of at most COL_RUN.
-void add_columns(std::vector<Column>& out, int b, int ncol, int e) {
+// columns per workgroup (or `per`), the axis cut into equal runs of at most
+// COL_RUN.
+void add_columns(std::vector<Column>& out, int b, int ncol, int e, int per = COL_THREADS) {
   const int k = (e + COL_RUN - 1) / COL_RUN;
   for (int p = 0; p < k; ++p)
-    for (int c = 0; c < ncol; c += COL_THREADS)
-      out.push_back(Column{b, c, std::min(c + COL_THREADS, ncol), (int)((long long)e * p / k),
+    for (int c = 0; c < ncol; c += per)
+      out.push_back(Column{b, c, std::min(c + per, ncol), (int)((long long)e * p / k),
                            (int)((long long)e * (p + 1) / k)});
 }
 
@@ -436,7 +437,8 @@ void build_front(ppm_ctx& c) {
 
 // The whole level's ranges of the fused front end's work lists.
 FrontRanges front_all(const ppm_ctx& c) {
-  return FrontRanges{0, (int)c.tilesX.size(), 0, (int)c.colsY.size(), 0, (int)c.colsZ.size()};
+  return FrontRanges{0, (int)c.tilesX.size(), 0, (int)c.colsY.size(), 0, (int)c.colsZ.size(),
+                     0, (int)c.colsF.size()};
 }
 
 void build_tiles(ppm_ctx& c) {
@@ -450,6 +452,8 @@ void build_tiles(ppm_ctx& c) {
   c.colsY.clear();
   c.tY_begin.assign(1, 0);
   c.colsZ.clear();
+  c.colsF.clear();
+  c.tCF_begin.assign(1, 0);
   c.tZ_begin.assign(1, 0);
   for (int b = 0; b < c.layout.nbox; ++b) {
     int n[3];
@@ -460,11 +464,13 @@ void build_tiles(ppm_ctx& c) {
     add_tiles(c.tilesXA, b, n[0] + 2, n[1] + 2, n[2] + 2, XF_OWNED - 1, c.strip_rows);
     add_columns(c.colsY, b, (n[0] + 2) * (n[2] + 2), n[1] + 2);
     add_columns(c.colsZ, b, (n[0] + 2) * (n[1] + 2), n[2] + 2);
+    add_columns(c.colsF, b, (n[0] + 2) * n[1], n[2], COL_FINAL);
     c.tS_begin.push_back((int)c.tilesS.size());
     c.tE_begin.push_back((int)c.tilesE.size());
     c.tX_begin.push_back((int)c.tilesX.size());
     c.tY_begin.push_back((int)c.colsY.size());
     c.tZ_begin.push_back((int)c.colsZ.size());
+    c.tCF_begin.push_back((int)c.colsF.size());
   }
 }
 
@@ -649,6 +655,7 @@ int ppm_ctx_create(const ppm_layout* layout, ppm_ctx** out) {
       (e = upload(&ctx->d_tilesXA, ctx->tilesXA)) != hipSuccess ||
       (e = upload(&ctx->d_colsY, ctx->colsY)) != hipSuccess ||
       (e = upload(&ctx->d_colsZ, ctx->colsZ)) != hipSuccess ||
+      (e = upload(&ctx->d_colsF, ctx->colsF)) != hipSuccess ||
       (e = upload(&ctx->d_desc, ctx->plan->desc)) != hipSuccess ||
       (e = upload(&ctx->d_start, ctx->plan->start)) != hipSuccess ||
       (e = hipMalloc((void**)&ctx->d_consts, sizeof(StepConsts))) != hipSuccess ||
@@ -678,6 +685,7 @@ int ppm_ctx_destroy(ppm_ctx* ctx) {
   (void)hipFree(ctx->d_tilesXA);
   (void)hipFree(ctx->d_colsY);
   (void)hipFree(ctx->d_colsZ);
+  (void)hipFree(ctx->d_colsF);
   (void)hipFree(ctx->d_bricks);
   (void)hipFree(ctx->d_fbricks);
   (void)hipFree(ctx->d_desc);
@@ -824,7 +832,7 @@ static int hydro_step_impl(ppm_ctx* ctx, const double* U, double* Unew, double* 
   } else {
     for (int b = 0; b < ctx->layout.nbox; ++b) {
       const FrontRanges fr{ctx->tX_begin[b], ctx->tX_begin[b + 1], ctx->tY_begin[b], ctx->tY_begin[b + 1],
-                           ctx->tZ_begin[b], ctx->tZ_begin[b + 1]};
+                           ctx->tZ_begin[b], ctx->tZ_begin[b + 1], ctx->tCF_begin[b], ctx->tCF_begin[b + 1]};
       rc = run(ctx->tS_begin[b], ctx->tS_begin[b + 1], ctx->tE_begin[b], ctx->tE_begin[b + 1], ctx->tB_begin[b],
                ctx->tB_begin[b + 1], ctx->tF_begin[b], ctx->tF_begin[b + 1], fr, nullptr);
       if (rc) return rc;
@@ -1177,16 +1185,19 @@ int ppm_set_tiling(ppm_ctx* ctx, int32_t tile, int32_t strip_rows) {
   (void)hipFree(ctx->d_tilesXA);
   (void)hipFree(ctx->d_colsY);
   (void)hipFree(ctx->d_colsZ);
+  (void)hipFree(ctx->d_colsF);
   ctx->d_tilesS = nullptr;
   ctx->d_tilesE = nullptr;
   ctx->d_tilesX = nullptr;
   ctx->d_tilesXA = nullptr;
   ctx->d_colsY = nullptr;
   ctx->d_colsZ = nullptr;
+  ctx->d_colsF = nullptr;
   if ((e = upload(&ctx->d_tilesS, ctx->tilesS)) != hipSuccess || (e = upload(&ctx->d_tilesE, ctx->tilesE)) != hipSuccess ||
       (e = upload(&ctx->d_tilesX, ctx->tilesX)) != hipSuccess ||
       (e = upload(&ctx->d_tilesXA, ctx->tilesXA)) != hipSuccess || (e = upload(&ctx->d_colsY, ctx->colsY)) != hipSuccess ||
-      (e = upload(&ctx->d_colsZ, ctx->colsZ)) != hipSuccess)
+      (e = upload(&ctx->d_colsZ, ctx->colsZ)) != hipSuccess ||
+      (e = upload(&ctx->d_colsF, ctx->colsF)) != hipSuccess)
     return ctx->hip(e, "tiling upload");
   return PPM_OK;
 }

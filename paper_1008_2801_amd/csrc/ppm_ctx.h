@@ -40,6 +40,8 @@ struct ppm_ctx {
   std::vector<Tile> tilesXA;            // adjoint along x: traced-grid runs of XF_OWNED - 1 zones
   std::vector<int> tX_begin;            // nbox + 1
   std::vector<Column> colsY, colsZ;     // front forms 2, 3: columns along y, z
+  std::vector<Column> colsF;            // final stage: columns along z
+  std::vector<int> tCF_begin;           // nbox + 1
   std::vector<int> tY_begin, tZ_begin;  // nbox + 1
   std::vector<Brick> bricks;
   std::vector<int> tB_begin;            // nbox + 1
@@ -71,6 +73,7 @@ struct ppm_ctx {
   Tile* d_tilesXA = nullptr;
   Column* d_colsY = nullptr;
   Column* d_colsZ = nullptr;
+  Column* d_colsF = nullptr;
   Brick* d_bricks = nullptr;
   Brick* d_fbricks = nullptr;
   FillDesc* d_desc = nullptr;
@@ -119,6 +122,7 @@ struct ppm_ctx {
     L.tilesXA = d_tilesXA;
     L.colsY = d_colsY;
     L.colsZ = d_colsZ;
+    L.colsF = d_colsF;
     L.desc = d_desc;
     L.desc_start = d_start;
     L.consts = d_consts;

@@ -75,6 +75,7 @@ constexpr int XF_OWNED = XF_THREADS / 64 * 63;
 // columns [c0, c1) (x slots fastest, then the third axis) and walk the slots
 // [k0, k1) of the axis
 constexpr int COL_THREADS = 256;
+constexpr int COL_FINAL = COL_THREADS / 64 * 62;  // columns a workgroup of the final stage owns
 constexpr int COL_RUN = 16;  // slots per run (8 and 32: 3% and 1% slower on 256^3 FP64)
 struct Column {
   int box;
@@ -83,6 +84,7 @@ struct Column {
 // ranges of the front forms' work lists of a launch
 struct FrontRanges {
   int x0, x1, y0, y1, z0, z1;
+  int f0, f1;  // columns of the final stage
 };
 __host__ __device__ inline int front_group(int mx, int my) {
   const int a = mx * my > mx + my ? mx * my : mx + my;
@@ -163,6 +165,7 @@ struct DevLevel {
   const Tile* tilesXA;  // runs of XF_OWNED - 1 traced zones (adjoint along x)
   const Column* colsY;  // columns along y and z (front forms 2, 3)
   const Column* colsZ;
+  const Column* colsF;  // columns along z of the final stage
   const FillDesc* desc;
   const long long* desc_start;  // exclusive prefix of zone counts, ndesc+1
   StepConsts* consts;

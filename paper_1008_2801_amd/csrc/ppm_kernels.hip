@@ -715,13 +715,12 @@ __global__ void __launch_bounds__(MAX_TILE) k_riemann3(const Tile* __restrict__ 
 }
 
 // O10 for one zone: U' = U - ((dt/h_x dFx + dt/h_y dFy) + dt/h_z dFz), then
-// the Heun constant-gravity source.
-__device__ __forceinline__ void update_zone(const double uo[5], const double fxd[5], const double fyd[5],
-                                            const double fzd[5], double dtdx0, double dtdx1, double dtdx2,
+// the Heun constant-gravity source.  df: the sum in the parentheses.
+__device__ __forceinline__ void update_zone(const double uo[5], const double df[5],
                                             const StepConsts* __restrict__ sc, int grav, double g0, double g1,
                                             double g2, double un[5]) {
 #pragma unroll
-  for (int m = 0; m < 5; ++m) un[m] = uo[m] - ((dtdx0 * fxd[m] + dtdx1 * fyd[m]) + dtdx2 * fzd[m]);
+  for (int m = 0; m < 5; ++m) un[m] = uo[m] - df[m];
   if (grav) {
     const double adt = sc->dt, hdt = sc->hdt;
     double s0[5], s1[5];
@@ -790,19 +789,20 @@ __device__ __forceinline__ double update_body(const Tile& tl, const DevBox& B, c
   const long long NS = (long long)N0 * N1 * N2;
   const long long ui = B.soff + ((long long)(z.x[2] + NG) * N1 + (z.x[1] + NG)) * N0 + (z.x[0] + NG);
   const S* w = work + B.eoff + z.e;
-  double fxd[5], fyd[5], fzd[5], uo[5];
+  double df[5], uo[5];
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     const S* f0 = w + (E_F3 + 0 * 5 + m) * LE;
     const S* f1 = w + (E_F3 + 1 * 5 + m) * LE;
     const S* f2 = w + (E_F3 + 2 * 5 + m) * LE;
-    fxd[m] = (double)f0[1] - (double)f0[0];
-    fyd[m] = (double)f1[sy] - (double)f1[0];
-    fzd[m] = (double)f2[sz] - (double)f2[0];
+    const double fxd = (double)f0[1] - (double)f0[0];
+    const double fyd = (double)f1[sy] - (double)f1[0];
+    const double fzd = (double)f2[sz] - (double)f2[0];
+    df[m] = (dtdx0 * fxd + dtdx1 * fyd) + dtdx2 * fzd;
     uo[m] = U[ui + m * NS];
   }
   double un[5];
-  update_zone(uo, fxd, fyd, fzd, dtdx0, dtdx1, dtdx2, sc, grav, g0, g1, g2, un);
+  update_zone(uo, df, sc, grav, g0, g1, g2, un);
 #pragma unroll
   for (int m = 0; m < 5; ++m) Unew[ui + m * NS] = un[m];
   if (!so.bits) return 0.0;
@@ -839,6 +839,207 @@ __global__ void __launch_bounds__(MAX_TILE) k_update(const Tile* __restrict__ ti
   if (so.bits) block_max_to(smax_lane, so.bits);
 }
 
+
+// O9 + O10 in columns along z: each lane owns the zones of a column in a run
+// of planes, 62 columns of a wavefront's 64 (the first and last lane serve
+// their x neighbours).  A zone's corrected states are formed once: the low
+// state of its x face comes from the lane below, the high x face's flux from
+// the lane above, the low state of its z face and its low z flux from the
+// plane before; the pair fluxes on its own z faces are kept from plane to
+// plane.  Only the y faces are solved by both zones they bound (four solves
+// per zone instead of three; an exchange through LDS, in bricks or streamed
+// with barriers, was slower).  The final fluxes never go to HBM and the lines
+// asked of L2 fall by a third.  The arithmetic is riemann3_face and
+// update_zone, so the results are the staged kernels' bit for bit.
+// 168 registers, 3 waves per SIMD: bound by the latency of a plane's dependent
+// loads.  Measured against riemann3 + update, FP64: 256^3 2.79 -> 2.56 ms, 216
+// boxes of 64^3 10.7 -> 8.6, 512 boxes of 16 to 64 zones per edge 3.62 -> 3.14.
+template <class S>
+__device__ __forceinline__ void load5(const S* __restrict__ w, long long LE, int plane, S v[5]) {
+#pragma unroll
+  for (int m = 0; m < 5; ++m) v[m] = w[(plane + m) * LE];
+}
+
+// The traced state of axis d on one side of the zone at w, corrected by the
+// pair flux differences D1 (t1) and D2 (t2).
+template <int d, int side, class S>
+__device__ __forceinline__ void stage3_state(const S* __restrict__ w, long long LE, const Gas<S>& G, const S D1[5],
+                                             S c1, const S D2[5], S c2, S q[5], int& fl) {
+  S qe[5], u[5];
+  load5(w, LE, E_TRACE + (d * 2 + side) * 5, qe);
+  prim_to_cons(qe, G, u);
+#pragma unroll
+  for (int m = 0; m < 5; ++m) u[m] = nmadd(c2, D2[m], nmadd(c1, D1[m], u[m]));
+  cons_to_prim_floor(u, G, q, fl);
+}
+
+template <class S>
+__device__ __forceinline__ void sub5(const S a[5], const S b[5], S d[5]) {
+#pragma unroll
+  for (int m = 0; m < 5; ++m) d[m] = a[m] - b[m];
+}
+// The next lane's value.
+template <class S> __device__ __forceinline__ S lane_up(S v) { return __shfl_down(v, 1, 64); }
+
+// Difference across the zone at w, along x, of the pair flux at `plane`.
+template <class S>
+__device__ __forceinline__ void pair_diff_x(const S* __restrict__ w, long long LE, int plane, S D[5]) {
+  S f[5];
+  load5(w, LE, plane, f);
+#pragma unroll
+  for (int m = 0; m < 5; ++m) D[m] = lane_up(f[m]) - f[m];
+}
+
+// Used in FP64, where its runs fill the card twice over (a 160^3 box, 1.4 times,
+// takes 800 us against 741 staged) and its planes leave the Infinity Cache.
+// FP32 stays staged: 256^3 1.56 ms against 1.63-1.73 (boxes of 64^3 gain 8%,
+// boxes of 40^3 lose 9%).
+bool final_columns_pay(long long LE, int groups) { return columns_pay<double>(LE, groups) && groups >= 1536; }
+
+template <class S>
+__global__ void __launch_bounds__(COL_THREADS) __attribute__((amdgpu_waves_per_eu(3)))
+k_final_columns(const Column* __restrict__ cols, int ncols, const DevBox* __restrict__ boxes,
+                const S* __restrict__ work, long long LE, Gas<S> G, const StepConsts* __restrict__ sc,
+                const double* __restrict__ U, double* __restrict__ Unew, double* fx, double* fy, double* fz, int grav,
+                double g0, double g1, double g2, SpeedOut so, int* flags) {
+  constexpr int XY = E_F2 + pair_index(0, 1) * 5, XZ = E_F2 + pair_index(0, 2) * 5, YX = E_F2 + pair_index(1, 0) * 5,
+                YZ = E_F2 + pair_index(1, 2) * 5, ZX = E_F2 + pair_index(2, 0) * 5, ZY = E_F2 + pair_index(2, 1) * 5;
+  const int t = xcd_tile(ncols);
+  if (t < 0) return;  // the whole workgroup
+  const Column C = cols[t];
+  const DevBox B = boxes[C.box];
+  const int lane = threadIdx.x & 63;
+  const int E0 = B.n[0] + 2, E1 = B.n[1] + 2, ncol = E0 * B.n[1];
+  // column: x slots fastest, then the valid rows; lanes beyond the columns
+  // repeat the nearest one (their values reach no owned zone)
+  const int cw = C.c0 + (int)(threadIdx.x >> 6) * 62 + lane - 1;
+  const int c = cw < 0 ? 0 : (cw >= ncol ? ncol - 1 : cw);
+  const int y = (int)div31((unsigned)c, B.de[0]), x = c - y * E0 - 1;
+  const bool own = lane >= 1 && lane <= 62 && cw < C.c1;
+  const bool face = own && x >= 0, zone = face && x < B.n[0];
+  const long long pl = (long long)E0 * E1;
+  const S* w = work + B.eoff + C.k0 * pl + (long long)(y + 1) * E0 + (x + 1);  // zone plane k0 - 1
+  const S c2x = SC<S>::dt2h(sc)[0], c2y = SC<S>::dt2h(sc)[1], c2z = SC<S>::dt2h(sc)[2];
+  const double dtdx0 = sc->dtdx[0], dtdx1 = sc->dtdx[1], dtdx2 = sc->dtdx[2];
+  const int N0 = B.n[0] + 2 * NG, N1 = B.n[1] + 2 * NG, N2 = B.n[2] + 2 * NG;
+  const long long NS = (long long)N0 * N1 * N2;
+  long long ui = B.soff + ((long long)(C.k0 + NG) * N1 + (y + NG)) * N0 + (x + NG);
+  int flz = 0, flx = 0;  // floors met on the zone's y and z faces, on its low x face
+  double s = 0.0;
+  S zhi[5], fzl[5], zy[5], zx1[5];  // carried from plane to plane
+  {
+    S Dxy[5], Dyx[5], a[5], b[5];
+    pair_diff_x(w, LE, XY, Dxy);
+    load5(w, LE, YX, a);
+    load5(w + E0, LE, YX, b);
+    sub5(b, a, Dyx);
+    stage3_state<2, 0>(w, LE, G, Dxy, c2x, Dyx, c2y, zhi, flz);
+    w += pl;  // zone plane k0
+    load5(w, LE, ZY, zy);
+    load5(w, LE, ZX, zx1);
+  }
+  // plane k - 1 owns the update of its zone; plane k gives its high z face
+  for (int k = C.k0; k <= C.k1; ++k, w += pl) {
+    S F[5], H[5];
+    {  // z face k
+      S Dxy[5], Dyx[5], a[5], b[5], lo[5];
+      pair_diff_x(w, LE, XY, Dxy);
+      load5(w, LE, YX, a);
+      load5(w + E0, LE, YX, b);
+      sub5(b, a, Dyx);
+      stage3_state<2, 1>(w, LE, G, Dxy, c2x, Dyx, c2y, lo, flz);
+      wall_states<2>(B, k, zhi, lo);
+      riemann<2>(zhi, lo, G, F, flz);
+      stage3_state<2, 0>(w, LE, G, Dxy, c2x, Dyx, c2y, zhi, flz);
+    }
+    if (fz && zone && (k > C.k0 || k == 0)) {
+      const int xs[3] = {x, y, k};
+      write_flux<2>(B, xs, F, fz);
+    }
+    double df[5];
+    if (k > C.k0) {
+      const S* v = w - pl;  // zone plane k - 1
+      // x faces
+      {
+        S Dyz[5], Dzy[5], a[5], b[5], lo[5], hi[5];
+        load5(v, LE, YZ, a);
+        load5(v + E0, LE, YZ, b);
+        sub5(b, a, Dyz);
+        load5(w, LE, ZY, a);
+#pragma unroll
+        for (int m = 0; m < 5; ++m) {
+          Dzy[m] = a[m] - zy[m];
+          zy[m] = a[m];
+        }
+        stage3_state<0, 0>(v, LE, G, Dyz, c2y, Dzy, c2z, hi, flx);
+        stage3_state<0, 1>(v, LE, G, Dyz, c2y, Dzy, c2z, lo, flx);
+#pragma unroll
+        for (int m = 0; m < 5; ++m) hi[m] = __shfl_up(hi[m], 1, 64);
+        wall_states<0>(B, x, hi, lo);
+        riemann<0>(hi, lo, G, H, flx);
+        if (fx && face) {
+          const int xs[3] = {x, y, k - 1};
+          write_flux<0>(B, xs, H, fx);
+        }
+#pragma unroll
+        for (int m = 0; m < 5; ++m) df[m] = dtdx0 * ((double)lane_up(H[m]) - (double)H[m]);
+      }
+      // y faces, low then high; zone row y in between serves both
+      {
+        S Dxz[5], Dzx[5], a[5], L[5], R[5], f[5];
+        pair_diff_x(v - E0, LE, XZ, Dxz);
+        load5(w - E0, LE, ZX, a);
+#pragma unroll
+        for (int m = 0; m < 5; ++m) Dzx[m] = a[m] - v[(ZX + m) * LE - E0];
+        stage3_state<1, 0>(v - E0, LE, G, Dxz, c2x, Dzx, c2z, L, flz);
+        pair_diff_x(v, LE, XZ, Dxz);
+        load5(w, LE, ZX, a);
+#pragma unroll
+        for (int m = 0; m < 5; ++m) {
+          Dzx[m] = a[m] - zx1[m];
+          zx1[m] = a[m];
+        }
+        stage3_state<1, 1>(v, LE, G, Dxz, c2x, Dzx, c2z, R, flz);
+        wall_states<1>(B, y, L, R);
+        riemann<1>(L, R, G, f, flz);
+        stage3_state<1, 0>(v, LE, G, Dxz, c2x, Dzx, c2z, L, flz);
+        pair_diff_x(v + E0, LE, XZ, Dxz);
+        load5(w + E0, LE, ZX, a);
+#pragma unroll
+        for (int m = 0; m < 5; ++m) Dzx[m] = a[m] - v[(ZX + m) * LE + E0];
+        stage3_state<1, 1>(v + E0, LE, G, Dxz, c2x, Dzx, c2z, R, flz);
+        wall_states<1>(B, y + 1, L, R);
+        riemann<1>(L, R, G, H, flz);
+        if (fy && zone) {
+          const int xs[3] = {x, y, k - 1}, xh[3] = {x, y + 1, k - 1};
+          write_flux<1>(B, xs, f, fy);
+          if (y + 1 == B.n[1]) write_flux<1>(B, xh, H, fy);
+        }
+#pragma unroll
+        for (int m = 0; m < 5; ++m) df[m] = df[m] + dtdx1 * ((double)H[m] - (double)f[m]);
+      }
+      if (zone) {
+        double uo[5], un[5];
+#pragma unroll
+        for (int m = 0; m < 5; ++m) {
+          df[m] = df[m] + dtdx2 * ((double)F[m] - (double)fzl[m]);
+          uo[m] = U[ui + m * NS];
+        }
+        update_zone(uo, df, sc, grav, g0, g1, g2, un);
+#pragma unroll
+        for (int m = 0; m < 5; ++m) Unew[ui + m * NS] = un[m];
+        if (so.bits)
+          s = smax(s, fold_signal_speed(0.0, un[0], un[1], un[2], un[3], un[4], so.h[0], so.h[1], so.h[2], so.gamma,
+                                        so.gm1, so.small_pres));
+      }
+      ui += (long long)N0 * N1;
+    }
+#pragma unroll
+    for (int m = 0; m < 5; ++m) fzl[m] = F[m];
+  }
+  raise_flags(flags, (zone ? flz : 0) | (face ? flx : 0));
+  if (so.bits) block_max_to(s, so.bits);
+}
 
 // O9 + O10 fused on a brick of valid zones: the final fluxes of every face
 // of the brick (its boundary faces are computed by both bricks that share
@@ -901,18 +1102,19 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_final_update(const Brick* __r
     const int iz = (l2 * e1 + l1) * e0 + l0;              // z-face below
     const long long ui = B.soff + ((long long)(K.o[2] + l2 + NG) * N1 + (K.o[1] + l1 + NG)) * N0 +
                          (K.o[0] + l0 + NG);
-    double fxd[5], fyd[5], fzd[5], uo[5], un[5];
+    double df[5], uo[5], un[5];
 #pragma unroll
     for (int m = 0; m < 5; ++m) {
       const S* F0 = Fs + m * BRICK_FACES;
       const S* F1 = Fs + (5 + m) * BRICK_FACES;
       const S* F2 = Fs + (10 + m) * BRICK_FACES;
-      fxd[m] = (double)F0[ix + 1] - (double)F0[ix];
-      fyd[m] = (double)F1[iy + e0] - (double)F1[iy];
-      fzd[m] = (double)F2[iz + e0 * e1] - (double)F2[iz];
+      const double fxd = (double)F0[ix + 1] - (double)F0[ix];
+      const double fyd = (double)F1[iy + e0] - (double)F1[iy];
+      const double fzd = (double)F2[iz + e0 * e1] - (double)F2[iz];
+      df[m] = (dtdx0 * fxd + dtdx1 * fyd) + dtdx2 * fzd;
       uo[m] = U[ui + m * NS];
     }
-    update_zone(uo, fxd, fyd, fzd, dtdx0, dtdx1, dtdx2, sc, grav, g0, g1, g2, un);
+    update_zone(uo, df, sc, grav, g0, g1, g2, un);
 #pragma unroll
     for (int m = 0; m < 5; ++m) Unew[ui + m * NS] = un[m];
     if (so.bits)
@@ -1013,16 +1215,17 @@ __global__ void __launch_bounds__(STREAM_MAX_THREADS) k_final_stream(
     for (int q = t; q < nz; q += nt) {
       const int j = q / ex, i = q - j * ex;
       const int x0 = K.o[0] + i, y0 = K.o[1] + j;
-      double fxd[5], fyd[5], fzd[5], uo[5], un[5];
+      double df[5], uo[5], un[5];
       const long long ui = B.soff + ((long long)(z + NG) * N1 + (y0 + NG)) * N0 + (x0 + NG);
 #pragma unroll
       for (int m = 0; m < 5; ++m) {
-        fxd[m] = (double)Fx[m * FXN + j * (sx + 1) + i + 1] - (double)Fx[m * FXN + j * (sx + 1) + i];
-        fyd[m] = (double)Fy[m * FYN + (j + 1) * sx + i] - (double)Fy[m * FYN + j * sx + i];
-        fzd[m] = (double)Fhi[m * FZN + j * sx + i] - (double)Flo[m * FZN + j * sx + i];
+        const double fxd = (double)Fx[m * FXN + j * (sx + 1) + i + 1] - (double)Fx[m * FXN + j * (sx + 1) + i];
+        const double fyd = (double)Fy[m * FYN + (j + 1) * sx + i] - (double)Fy[m * FYN + j * sx + i];
+        const double fzd = (double)Fhi[m * FZN + j * sx + i] - (double)Flo[m * FZN + j * sx + i];
+        df[m] = (dtdx0 * fxd + dtdx1 * fyd) + dtdx2 * fzd;
         uo[m] = U[ui + m * NS];
       }
-      update_zone(uo, fxd, fyd, fzd, dtdx0, dtdx1, dtdx2, sc, grav, g0, g1, g2, un);
+      update_zone(uo, df, sc, grav, g0, g1, g2, un);
 #pragma unroll
       for (int m = 0; m < 5; ++m) Unew[ui + m * NS] = un[m];
       if (so.bits)
@@ -1210,6 +1413,17 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
     if (ev) (void)hipEventRecord(ev[6], s);
     if (ev) (void)hipEventRecord(ev[7], s);
     return hipGetLastError();
+  }
+  if constexpr (sizeof(S) == 8) {
+    const int nCol = fr.f1 - fr.f0;
+    if (upto == STEP_FULL && final_columns_pay(L.LE, nCol)) {
+      hipLaunchKernelGGL(k_final_columns<S>, dim3(xcd_grid(nCol)), dim3(COL_THREADS), 0, s, L.colsF + fr.f0, nCol,
+                         L.boxes, (const S*)ework, L.LE, G, L.consts, U, Unew, fx, fy, fz, G.grav, g[0], g[1], g[2],
+                         so, L.flags);
+      if (ev) (void)hipEventRecord(ev[6], s);
+      if (ev) (void)hipEventRecord(ev[7], s);
+      return hipGetLastError();
+    }
   }
   hipLaunchKernelGGL(k_riemann3<S>, dim3(xcd_grid(nE), 3), blk, 0, s, TE, nE, L.boxes, ework, L.LE, G,
                      L.consts, fx, fy, fz, L.flags);

@@ -75,3 +75,22 @@ def test_bricks_one_zone_thin_agree_bitwise(tiling):
     got = _step(lay, h, U, p, P.BATCHED, 0, form=1)
     for a, b in zip(list(ref[:3]) + list(ref[3]), list(got[:3]) + list(got[3])):
         assert torch.equal(a, b), tiling
+
+
+@pytest.mark.parametrize("tiling", [([200], [181], [195]), ([130, 3, 61], [1, 40, 90], [65, 33, 16, 2, 63])])
+def test_final_columns_agree_bitwise(tiling):
+    """Levels large enough for the final stage in columns (form 0) against the
+    brick form: new state, flux outputs, next dt, and the saved adjoint."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    # the final stage's rule: planes of 16 MB, 1536 workgroups of 248 columns in runs of 16 planes
+    groups = sum(-(-((x + 2) * y) // 248) * -(-z // 16) for x in tiling[0] for y in tiling[1] for z in tiling[2])
+    zones = sum((x + 2) * (y + 2) * (z + 2) for x in tiling[0] for y in tiling[1] for z in tiling[2])
+    assert zones * 8 >= 16 << 20 and groups >= 1536, (zones, groups)
+    lay, h, U, p = _level(tiling, 0)
+    ref = _step(lay, h, U, p, P.BATCHED, 0, form=1)
+    got = _step(lay, h, U, p, P.BATCHED, 2)
+    for a, b in zip(ref[:3], got[:3]):
+        assert torch.equal(a, b), tiling
+    for a, b in zip(ref[3], got[3]):
+        assert torch.equal(a, b), tiling
