@@ -778,6 +778,12 @@ int ppm_compute_dt(ppm_ctx* ctx, const double* U, const double dx[3], const ppm_
   return rc;
 }
 
+static StepStart step_start(double dt, const double* dt_dev, const double dx[3], const ppm_params* params,
+                            unsigned long long* clear) {
+  StepStart st{true, dt, dt_dev, {dx[0], dx[1], dx[2]}, {params->grav[0], params->grav[1], params->grav[2]}, clear};
+  return st;
+}
+
 // work: the step workspace (null: the context's, ppm_set_workspace) and its
 // size; timed: record profiling events when profiling is on.
 static int hydro_step_impl(ppm_ctx* ctx, const double* U, double* Unew, double* const* flux, double dt,
@@ -806,22 +812,17 @@ static int hydro_step_impl(ppm_ctx* ctx, const double* U, double* Unew, double* 
   if (!m.empty()) return ctx->fail(PPM_EINVAL, m);
   hipStream_t s = (hipStream_t)stream;
   const DevLevel L = ctx->level();
-  int rc = ctx->hip(launch_step_consts(L, dt, dt_dev, dx, params->grav, s), "step consts");
-  if (rc) return rc;
+  int rc = PPM_OK;
   SpeedOut so{nullptr, {dx[0], dx[1], dx[2]}, params->gamma, params->gamma - 1.0, params->small_pres};
-  if (dt_next) {
-    // after the step constants have read dt_dev, which dt_next may alias
-    so.bits = (unsigned long long*)(dt_next + 1);
-    rc = ctx->hip(launch_speed_clear(so.bits, s), "next dt");
-    if (rc) return rc;
-  }
+  if (dt_next) so.bits = (unsigned long long*)(dt_next + 1);
+  StepStart st = step_start(dt, dt_dev, dx, params, so.bits);
   const int grav = (params->grav[0] != 0.0 || params->grav[1] != 0.0 || params->grav[2] != 0.0) ? 1 : 0;
   auto run = [&](int tS0, int tS1, int tE0, int tE1, int tB0, int tB1, int tF0, int tF1, const FrontRanges& fr,
                  hipEvent_t* ev) {
     return ctx->hip(launch_step(L, params->precision, tS0, tS1, tE0, tE1, tB0, tB1, tF0, tF1, fr, U, Unew, flux,
                                 work,
                                 params->gamma, params->small_dens, params->small_pres, params->limiter,
-                                params->flattening, params->riemann_iters, grav, params->grav, s, ev, upto, so),
+                                params->flattening, params->riemann_iters, grav, params->grav, s, ev, upto, so, st),
                     "step");
   };
   if (mode == PPM_LAUNCH_BATCHED) {
@@ -836,6 +837,7 @@ static int hydro_step_impl(ppm_ctx* ctx, const double* U, double* Unew, double* 
       rc = run(ctx->tS_begin[b], ctx->tS_begin[b + 1], ctx->tE_begin[b], ctx->tE_begin[b + 1], ctx->tB_begin[b],
                ctx->tB_begin[b + 1], ctx->tF_begin[b], ctx->tF_begin[b + 1], fr, nullptr);
       if (rc) return rc;
+      st.on = false;  // the first box's launches started the step
     }
   }
   if (dt_next) return ctx->hip(launch_speed_finish(dt_next, params->cfl, s), "next dt");
@@ -989,8 +991,7 @@ static int adjoint_step(ppm_ctx* ctx, const double* U, const double* Unew_bar, c
   if (!m.empty()) return ctx->fail(PPM_EINVAL, m);
   hipStream_t s = (hipStream_t)stream;
   const DevLevel L = ctx->level();
-  int rc = ctx->hip(launch_step_consts(L, dt, dt_dev, dx, params->grav, s), "adjoint consts");
-  if (rc) return rc;
+  int rc = PPM_OK;
   const int grav = (params->grav[0] != 0.0 || params->grav[1] != 0.0 || params->grav[2] != 0.0) ? 1 : 0;
   const int nS = (int)ctx->tilesS.size(), nE = (int)ctx->tilesE.size();
   // recompute the forward intermediates through stage 2 (U is not written),
@@ -1000,8 +1001,11 @@ static int adjoint_step(ppm_ctx* ctx, const double* U, const double* Unew_bar, c
                               U, nullptr, nullptr, ctx->work,
                               params->gamma, params->small_dens, params->small_pres, params->limiter,
                               params->flattening, params->riemann_iters, grav, params->grav, s, nullptr,
-                              STEP_TO_STAGE2),
+                              STEP_TO_STAGE2, SpeedOut{}, step_start(dt, dt_dev, dx, params, nullptr)),
                   "adjoint recompute");
+    if (rc) return rc;
+  } else {
+    rc = ctx->hip(launch_step_consts(L, dt, dt_dev, dx, params->grav, s), "adjoint consts");
     if (rc) return rc;
   }
   FluxBar fb{{nullptr, nullptr, nullptr}};

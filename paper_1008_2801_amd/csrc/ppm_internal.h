@@ -212,16 +212,25 @@ struct SpeedOut {
   double gamma, gm1, small_pres;
 };
 
+// What the first launch of a step does besides its conversion: the step's
+// constants (L.consts) from dt (dt_dev[0] if given), the spacings and gravity,
+// and the next dt's accumulator cleared.
+struct StepStart {
+  bool on;
+  double dt;
+  const double* dt_dev;
+  double h[3], g[3];
+  unsigned long long* clear;
+};
+
 hipError_t launch_step(const DevLevel& L, int precision, int tS0, int tS1, int tE0, int tE1, int tB0, int tB1,
                        int tF0, int tF1, const FrontRanges& fr,
                        const double* U, double* Unew, double* const* flux, void* work,
                        const double gamma, const double small_dens, const double small_pres,
                        int limiter, int flattening, int iters, int grav, const double g[3],
-                       hipStream_t s, hipEvent_t* ev, int upto = STEP_FULL,
-                       SpeedOut so = SpeedOut{nullptr, {0.0, 0.0, 0.0}, 0.0, 0.0, 0.0});
-// The speed accumulator of a fused-dt step: cleared before the step's
-// launches, turned into dt = cfl / s after them (one lane each).
-hipError_t launch_speed_clear(unsigned long long* bits, hipStream_t s);
+                       hipStream_t s, hipEvent_t* ev, int upto, SpeedOut so, const StepStart& st);
+// The speed accumulator of a fused-dt step turned into dt = cfl / s after the
+// step's launches (one lane; the step's start clears it).
 hipError_t launch_speed_finish(double* dt_dev, double cfl, hipStream_t s);
 // Adjoint of one FP64 step (ppm_adjoint.hip); the forward workspace must hold
 // the recomputed prim..riemann2 intermediates of the same step.

@@ -107,7 +107,17 @@ template <class S>
 __global__ void __launch_bounds__(MAX_TILE) k_prim(const Tile* __restrict__ tiles, int ntiles,
                                                const DevBox* __restrict__ boxes,
                                                const double* __restrict__ U, S* __restrict__ prim,
-                                               long long LS, Gas<S> G, int* flags) {
+                                               long long LS, Gas<S> G, int* flags, StepStart st,
+                                               StepConsts* consts) {
+  // one workgroup more than the tiles need starts the step: a launch of its
+  // own costs 4.7 us between the others
+  if (st.on && blockIdx.x == gridDim.x - 1) {
+    if (threadIdx.x == 0) {
+      step_consts(consts, st.dt, st.dt_dev, st.h[0], st.h[1], st.h[2], st.g[0], st.g[1], st.g[2]);
+      if (st.clear) *st.clear = 0ull;  // after dt was read, which may lie beside it
+    }
+    return;
+  }
   prim_body(xcd_tile(ntiles), tiles, boxes, U, prim, LS, G, flags);
 }
 
@@ -1343,7 +1353,7 @@ template <class S>
 hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int tB0, int tB1, int tF0, int tF1,
                      const FrontRanges& fr, const double* U,
                      double* Unew, double* const* flux, void* work, Gas<S> G, const double g[3], hipStream_t s,
-                     hipEvent_t* ev, int upto, const SpeedOut& so) {
+                     hipEvent_t* ev, int upto, const SpeedOut& so, const StepStart& st) {
   S* prim = (S*)work;
   S* ework = prim + P_PLANES * L.LS;
   const int nS = tS1 - tS0, nE = tE1 - tE0;
@@ -1352,7 +1362,8 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
   if (nS <= 0 || nE <= 0) return hipSuccess;
   const dim3 blk(L.tile);
   if (ev) (void)hipEventRecord(ev[0], s);
-  hipLaunchKernelGGL(k_prim<S>, dim3(xcd_grid(nS)), blk, 0, s, TS, nS, L.boxes, U, prim, L.LS, G, L.flags);
+  hipLaunchKernelGGL(k_prim<S>, dim3(xcd_grid(nS) + (st.on ? 1 : 0)), blk, 0, s, TS, nS, L.boxes, U, prim, L.LS, G,
+                     L.flags, st, L.consts);
   if (ev) (void)hipEventRecord(ev[1], s);
   hipLaunchKernelGGL(k_flatten<S>, dim3(xcd_grid(nE)), blk, 0, s, TE, nE, L.boxes, prim, L.LS, ework, L.LE, G);
   if (ev) (void)hipEventRecord(ev[2], s);
@@ -1471,19 +1482,14 @@ hipError_t launch_step(const DevLevel& L, int precision, int tS0, int tS1, int t
                        void* work,
                        const double gamma, const double small_dens, const double small_pres, int limiter,
                        int flattening, int iters, int grav, const double g[3], hipStream_t s, hipEvent_t* ev,
-                       int upto, SpeedOut so) {
+                       int upto, SpeedOut so, const StepStart& st) {
   if (precision == 1)
     return step_impl<float>(L, tS0, tS1, tE0, tE1, tB0, tB1, tF0, tF1, fr, U, Unew, flux, work,
                             make_gas<float>(gamma, small_dens, small_pres, limiter, flattening, iters, grav),
-                            g, s, ev, upto, so);
+                            g, s, ev, upto, so, st);
   return step_impl<double>(L, tS0, tS1, tE0, tE1, tB0, tB1, tF0, tF1, fr, U, Unew, flux, work,
                            make_gas<double>(gamma, small_dens, small_pres, limiter, flattening, iters, grav),
-                           g, s, ev, upto, so);
-}
-
-hipError_t launch_speed_clear(unsigned long long* bits, hipStream_t s) {
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, bits);
-  return hipGetLastError();
+                           g, s, ev, upto, so, st);
 }
 
 hipError_t launch_speed_finish(double* dt_dev, double cfl, hipStream_t s) {
