@@ -324,11 +324,10 @@ __global__ void __launch_bounds__(MAX_TILE) __attribute__((amdgpu_waves_per_eu(8
 // Same arithmetic as trace_at and stage1_face, so the same bits as the
 // staged trace and riemann1 kernels along x.
 template <class S>
-__global__ void __launch_bounds__(XF_THREADS) k_front_x(const Tile* __restrict__ tiles, int ntiles,
-                                                    const DevBox* __restrict__ boxes, const S* __restrict__ prim,
-                                                    long long LS, S* __restrict__ work, long long LE, Gas<S> G,
-                                                    const StepConsts* __restrict__ sc, int* flags) {
-  const int t = xcd_tile(ntiles);
+__device__ __forceinline__ void front_x_body(int t, const Tile* __restrict__ tiles,
+                                             const DevBox* __restrict__ boxes, const S* __restrict__ prim,
+                                             long long LS, S* __restrict__ work, long long LE, const Gas<S>& G,
+                                             const StepConsts* __restrict__ sc, int* flags) {
   if (t < 0) return;  // the whole workgroup
   const Tile tl = tiles[t];
   const DevBox B = boxes[tl.box];
@@ -354,6 +353,61 @@ __global__ void __launch_bounds__(XF_THREADS) k_front_x(const Tile* __restrict__
   for (int m = 0; m < 5; ++m) L[m] = __shfl_up(qp[m], 1, 64);
   if (own && x >= 0) stage1_face<0>(B, x, L, qm, G, work, LE, idx, fl);
   raise_flags(flags, fl);
+}
+
+template <class S>
+__global__ void __launch_bounds__(XF_THREADS) k_front_x(const Tile* __restrict__ tiles, int ntiles,
+                                                    const DevBox* __restrict__ boxes, const S* __restrict__ prim,
+                                                    long long LS, S* __restrict__ work, long long LE, Gas<S> G,
+                                                    const StepConsts* __restrict__ sc, int* flags) {
+  front_x_body(xcd_tile(ntiles), tiles, boxes, prim, LS, work, LE, G, sc, flags);
+}
+
+// O4 + O5 + O7 along d (y or z) for one zone per lane: the lane traces its
+// zone and once more the zone below, whose high-face state its stage-1 problem
+// takes.
+template <int d, class S>
+__device__ __forceinline__ void front_zone_body(int t, const Tile* __restrict__ tiles,
+                                                const DevBox* __restrict__ boxes, const S* __restrict__ prim,
+                                                long long LS, S* __restrict__ work, long long LE, const Gas<S>& G,
+                                                const StepConsts* __restrict__ sc, int* flags) {
+  const Tile tl = tiles[t];
+  const DevBox B = boxes[tl.box];
+  EZone z;
+  if (!ezone(tl, B, z)) return;
+  S L[5], qp[5], qm[5];
+  int fl = 0;
+  if (z.x[d] >= 0) {
+    int below = 0;  // that zone's own lane raises its flags
+    trace_at<d>(B, z.x[0], z.x[1] - (d == 1), z.x[2] - (d == 2), z.e - stride(z.E, d), prim, LS, work, LE, G, sc, L,
+                qm, below);
+  }
+  trace_at<d>(B, z.x[0], z.x[1], z.x[2], z.e, prim, LS, work, LE, G, sc, qp, qm, fl);
+  store_traced<d>(work, LE, B, z.e, qp, qm);
+  if (z.x[d] >= 0) stage1_face<d>(B, z.x[d], L, qm, G, work, LE, z.e, fl);
+  raise_flags(flags, fl);
+}
+
+// The front end of a small level in one launch: the x axis's workgroups (nX
+// tiles), then y's and z's (nE tiles each).  Three launches one after the other
+// are bound by their start and their chain of dependent loads and solves, not
+// by their arithmetic, so tracing every zone twice along y and z costs less
+// than the launch that would have stored the states first.
+template <class S>
+__global__ void __launch_bounds__(XF_THREADS) k_front_small(const Tile* __restrict__ tilesX, int nX,
+                                                        const Tile* __restrict__ tilesE, int nE,
+                                                        const DevBox* __restrict__ boxes,
+                                                        const S* __restrict__ prim, long long LS,
+                                                        S* __restrict__ work, long long LE, Gas<S> G,
+                                                        const StepConsts* __restrict__ sc, int* flags) {
+  const int t = xcd_tile(nX + 2 * nE);
+  if (t < 0) return;
+  if (t < nX)
+    front_x_body(t, tilesX, boxes, prim, LS, work, LE, G, sc, flags);
+  else if (t < nX + nE)
+    front_zone_body<1>(t - nX, tilesE, boxes, prim, LS, work, LE, G, sc, flags);
+  else
+    front_zone_body<2>(t - nX - nE, tilesE, boxes, prim, LS, work, LE, G, sc, flags);
 }
 
 // O4 + O5 + O7 along d (y or z) in one kernel: each lane walks a column of
@@ -434,6 +488,15 @@ template <class S>
 bool columns_pay(long long LE, int groups) {
   return LE * (long long)sizeof(S) >= (16ll << 20) && groups >= 1024;
 }
+
+// Whether the front end takes one launch (k_front_small): with at most eight
+// workgroups per CU, about what the chip holds at once.  Kernel times (us),
+// k_front_x + k_trace + k_riemann1 -> k_front_small, FP64 unless named, by
+// workgroups: 470 (32^3) 22 -> 14.6; 870 (40^3) 28.7 -> 23.6; 1470 (48^3)
+// 33.2 -> 31.7, FP32 26.3 -> 22.3; 1650 (8 boxes of 24^3) 36.2 -> 36.0; but
+// 3370 (64^3) 53 -> 60, FP32 40.5 -> 40.1; 4680 (256x256x4) 64 -> 68.  Two
+// launches fewer save 3 us more.
+bool front_small_pays(int groups) { return groups <= 2048; }
 
 // y columns first (ny of them), then z columns.
 template <class S>
@@ -1382,10 +1445,16 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
     // z's in columns always (3) or where that pays (2) (timed in the trace slot)
     const int nX = fr.x1 - fr.x0, nY = fr.y1 - fr.y0, nZ = fr.z1 - fr.z0;
     const int d0 = (L.front >= 2 && nX > 0) ? 1 : 0;
-    if (d0)
+    const bool columns = d0 && nY + nZ > 0 && (L.front == 3 || columns_pay<S>(L.LE, nY + nZ));
+    const bool small = d0 && !columns && L.tile == XF_THREADS && front_small_pays(nX + 2 * nE);
+    if (d0 && !small)
       hipLaunchKernelGGL(k_front_x<S>, dim3(xcd_grid(nX)), dim3(XF_THREADS), 0, s, L.tilesX + fr.x0, nX, L.boxes,
                          (const S*)prim, L.LS, ework, L.LE, G, L.consts, L.flags);
-    if (d0 && nY + nZ > 0 && (L.front == 3 || columns_pay<S>(L.LE, nY + nZ))) {
+    if (small) {
+      hipLaunchKernelGGL(k_front_small<S>, dim3(xcd_grid(nX + 2 * nE)), dim3(XF_THREADS), 0, s, L.tilesX + fr.x0, nX,
+                         TE, nE, L.boxes, (const S*)prim, L.LS, ework, L.LE, G, L.consts, L.flags);
+      if (ev) (void)hipEventRecord(ev[3], s);
+    } else if (columns) {
       hipLaunchKernelGGL(k_front_yz<S>, dim3(xcd_grid(nY + nZ)), dim3(COL_THREADS), 0, s, L.colsY + fr.y0, nY,
                          L.colsZ + fr.z0, nZ, L.boxes, (const S*)prim, L.LS, ework, L.LE, G, L.consts, L.flags);
       if (ev) (void)hipEventRecord(ev[3], s);

@@ -94,3 +94,21 @@ def test_final_columns_agree_bitwise(tiling):
         assert torch.equal(a, b), tiling
     for a, b in zip(ref[3], got[3]):
         assert torch.equal(a, b), tiling
+
+
+# one zone; up to, at and beyond the zones of one workgroup; the most
+# workgroups the one-launch front end takes (2048) and a few more
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("tiling", [([4], [4], [4]), ([1, 3], [4], [4]), ([14], [14], [15]), ([5, 1], [70, 2], [3, 9]),
+                                    ([54], [53], [53]), ([55], [55], [55])])
+def test_front_end_in_one_launch_agrees_bitwise(tiling, precision):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lay, h, U, p = _level(tiling, precision)
+    for mode in (P.BATCHED, P.PER_BOX):
+        ref = _step(lay, h, U, p, mode, 0)
+        got = _step(lay, h, U, p, mode, 2)
+        for a, b in zip(ref[:3], got[:3]):
+            assert torch.equal(a, b), (tiling, precision, mode)
+        for a, b in zip(ref[3], got[3]):
+            assert torch.equal(a, b), (tiling, precision, mode)
