@@ -106,15 +106,14 @@ def record_traffic(fetch_csv, write_csv, kernel, workload, tiling, fetch_factor,
     def step_bytes(path, counter, factor):
         # every kernel of the steps, per step: the counted dispatches over
         # the step count, which the kernel's own dispatches give.  A
-        # stand-alone dt pass (k_zero_u64, k_wavespeed, k_finish_dt) is not
-        # part of a step; the speed pass that the brick form runs after its
-        # update is.
+        # stand-alone dt pass (k_clear_speed, k_wavespeed) is not part of a
+        # step.
         rows = sorted((r for r in csv.DictReader(open(path))
                        if r["Counter_Name"] == counter and "ppm::" in r["Kernel_Name"]),
                       key=lambda r: int(r["Dispatch_Id"]))
         tot = 0.0
-        for i, r in enumerate(rows):
-            if "k_wavespeed" in r["Kernel_Name"] and i > 0 and "k_zero_u64" in rows[i - 1]["Kernel_Name"]:
+        for r in rows:
+            if "k_wavespeed" in r["Kernel_Name"] or "k_clear_speed" in r["Kernel_Name"]:
                 continue
             tot += float(r["Counter_Value"])
         return tot * 1024 * factor

@@ -203,24 +203,25 @@ hipError_t launch_compute_dt(const DevLevel& L, int tile_begin, int tile_end, co
 // level asks for it), STEP_FULL_STAGED (the whole step with the final
 // fluxes left in the workspace, as the species stages need).
 enum { STEP_TO_STAGE2 = 5, STEP_FULL = 7, STEP_FULL_STAGED = 8 };
-// Optional output of the staged update: the maximum over the updated valid
-// zones of the signal speed max_d (|u_d| + c) / h_d, as the bits of a
-// non-negative double, max-accumulated into *bits (null: not computed).
+// Optional output of the update (dt null: not computed): dt[1], the maximum
+// over the updated valid zones of the signal speed max_d (|u_d| + c) / h_d, and
+// dt[0] = cfl / dt[1].
 struct SpeedOut {
-  unsigned long long* bits;
+  double* dt;
+  double cfl;
   double h[3];
   double gamma, gm1, small_pres;
 };
 
 // What the first launch of a step does besides its conversion: the step's
 // constants (L.consts) from dt (dt_dev[0] if given), the spacings and gravity,
-// and the next dt's accumulator cleared.
+// and the next dt's pair cleared (dt_next, when not null).
 struct StepStart {
   bool on;
   double dt;
   const double* dt_dev;
   double h[3], g[3];
-  unsigned long long* clear;
+  double* dt_next;
 };
 
 hipError_t launch_step(const DevLevel& L, int precision, int tS0, int tS1, int tE0, int tE1, int tB0, int tB1,
@@ -229,9 +230,6 @@ hipError_t launch_step(const DevLevel& L, int precision, int tS0, int tS1, int t
                        const double gamma, const double small_dens, const double small_pres,
                        int limiter, int flattening, int iters, int grav, const double g[3],
                        hipStream_t s, hipEvent_t* ev, int upto, SpeedOut so, const StepStart& st);
-// The speed accumulator of a fused-dt step turned into dt = cfl / s after the
-// step's launches (one lane; the step's start clears it).
-hipError_t launch_speed_finish(double* dt_dev, double cfl, hipStream_t s);
 // Adjoint of one FP64 step (ppm_adjoint.hip); the forward workspace must hold
 // the recomputed prim..riemann2 intermediates of the same step.
 size_t adjoint_workspace_bytes(long long LS, long long LE, int precision);

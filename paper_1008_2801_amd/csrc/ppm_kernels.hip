@@ -59,6 +59,12 @@ __global__ void __launch_bounds__(64) k_step_consts(StepConsts* c, double dt, co
   if (threadIdx.x == 0) step_consts(c, dt, dt_dev, h0, h1, h2, g0, g1, g2);
 }
 
+// Before the first block_speed_to: no speed yet, any step.
+__device__ __forceinline__ void clear_speed(double* dt) {
+  dt[0] = __builtin_inf();
+  dt[1] = 0.0;
+}
+
 // O2 on every stored zone: (rho, u, v, w, p) planes.  The sound speed is
 // formed here for the range check only: the stages that use it form it again
 // from rho and p (one plane less to write and to read).
@@ -114,7 +120,7 @@ __global__ void __launch_bounds__(MAX_TILE) k_prim(const Tile* __restrict__ tile
   if (st.on && blockIdx.x == gridDim.x - 1) {
     if (threadIdx.x == 0) {
       step_consts(consts, st.dt, st.dt_dev, st.h[0], st.h[1], st.h[2], st.g[0], st.g[1], st.g[2]);
-      if (st.clear) *st.clear = 0ull;  // after dt was read, which may lie beside it
+      if (st.dt_next) clear_speed(st.dt_next);  // after dt was read, which may be the same
     }
     return;
   }
@@ -831,11 +837,15 @@ __device__ __forceinline__ double fold_signal_speed(double s, double r, double m
   return smax(smax(smax(s, sx), sy), sz);
 }
 
-// Maximum of s over the workgroup, max-accumulated into *bits (the bits of
-// a non-negative double order like the doubles).  One atomic per
-// workgroup, skipped when the running maximum is already as large.  Every
-// lane of the workgroup must call it.
-__device__ __forceinline__ void block_max_to(double s, unsigned long long* bits) {
+// Maximum of s over the workgroup, folded into dt[1], the largest signal speed
+// so far, and dt[0], the time step cfl / dt[1] it allows.  Rounded division
+// never orders two steps against their speeds, so the least step over the
+// workgroups is the one of the largest speed bit for bit, and no launch has to
+// divide after them.  The bits of non-negative doubles order like the doubles:
+// a maximum of integers per workgroup, skipped when the running maximum is
+// already as large, and a minimum only from those that raised it (one from each
+// costs a 256 x 256 x 4 step 7 us).  Every lane of the workgroup must call it.
+__device__ __forceinline__ void block_speed_to(double s, double* dt, double cfl) {
   for (int off = 32; off > 0; off >>= 1) s = smax(s, __shfl_xor(s, off, 64));
   __shared__ double wmax[MAX_TILE / 64];
   if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = s;
@@ -844,12 +854,14 @@ __device__ __forceinline__ void block_max_to(double s, unsigned long long* bits)
     double m = wmax[0];
     for (int w = 1; w < (int)(blockDim.x / 64); ++w) m = smax(m, wmax[w]);
     const unsigned long long mb = (unsigned long long)__double_as_longlong(m);
-    if (mb > __hip_atomic_load(bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(bits, mb);
+    unsigned long long* bits = (unsigned long long*)dt;
+    if (mb > __hip_atomic_load(bits + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) && mb > atomicMax(bits + 1, mb))
+      atomicMin(bits, (unsigned long long)__double_as_longlong(cfl / m));
   }
 }
 
 // The update of one valid zone; returns its signal speed folded into 0 when
-// so.bits is set (else 0).
+// so.dt is set (else 0).
 template <class S>
 __device__ __forceinline__ double update_body(const Tile& tl, const DevBox& B, const EZone& z,
                                               const double* __restrict__ U, double* __restrict__ Unew,
@@ -878,13 +890,13 @@ __device__ __forceinline__ double update_body(const Tile& tl, const DevBox& B, c
   update_zone(uo, df, sc, grav, g0, g1, g2, un);
 #pragma unroll
   for (int m = 0; m < 5; ++m) Unew[ui + m * NS] = un[m];
-  if (!so.bits) return 0.0;
+  if (!so.dt) return 0.0;
   return fold_signal_speed(0.0, un[0], un[1], un[2], un[3], un[4], so.h[0], so.h[1], so.h[2], so.gamma, so.gm1,
                            so.small_pres);
 }
 
 // The update of the valid zones of tile tt; returns the lane's signal speed
-// (0 without so.bits or off the valid zones).
+// (0 without so.dt or off the valid zones).
 template <class S>
 __device__ __forceinline__ double update_tile(int tt, const Tile* __restrict__ tiles,
                                               const DevBox* __restrict__ boxes, const double* __restrict__ U,
@@ -909,7 +921,7 @@ __global__ void __launch_bounds__(MAX_TILE) k_update(const Tile* __restrict__ ti
   const int tt = xcd_tile(ntiles);
   if (tt < 0) return;  // the whole workgroup
   const double smax_lane = update_tile(tt, tiles, boxes, U, Unew, work, LE, sc, grav, g0, g1, g2, so);
-  if (so.bits) block_max_to(smax_lane, so.bits);
+  if (so.dt) block_speed_to(smax_lane, so.dt, so.cfl);
 }
 
 
@@ -1101,7 +1113,7 @@ k_final_columns(const Column* __restrict__ cols, int ncols, const DevBox* __rest
         update_zone(uo, df, sc, grav, g0, g1, g2, un);
 #pragma unroll
         for (int m = 0; m < 5; ++m) Unew[ui + m * NS] = un[m];
-        if (so.bits)
+        if (so.dt)
           s = smax(s, fold_signal_speed(0.0, un[0], un[1], un[2], un[3], un[4], so.h[0], so.h[1], so.h[2], so.gamma,
                                         so.gm1, so.small_pres));
       }
@@ -1111,13 +1123,13 @@ k_final_columns(const Column* __restrict__ cols, int ncols, const DevBox* __rest
     for (int m = 0; m < 5; ++m) fzl[m] = F[m];
   }
   raise_flags(flags, (zone ? flz : 0) | (face ? flx : 0));
-  if (so.bits) block_max_to(s, so.bits);
+  if (so.dt) block_speed_to(s, so.dt, so.cfl);
 }
 
 // O9 + O10 fused on a brick of valid zones: the final fluxes of every face
 // of the brick (its boundary faces are computed by both bricks that share
 // them) go to LDS instead of HBM, then each zone of the brick is updated
-// from them and, with so.bits, its signal speed folded into the next dt's
+// from them and, with so.dt, its signal speed folded into the next dt's
 // maximum.  The arithmetic is riemann3_face, update_zone and
 // fold_signal_speed, so the results are those of the staged kernels bit for
 // bit.
@@ -1190,11 +1202,11 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_final_update(const Brick* __r
     update_zone(uo, df, sc, grav, g0, g1, g2, un);
 #pragma unroll
     for (int m = 0; m < 5; ++m) Unew[ui + m * NS] = un[m];
-    if (so.bits)
+    if (so.dt)
       smax_lane = smax(smax_lane, fold_signal_speed(0.0, un[0], un[1], un[2], un[3], un[4], so.h[0], so.h[1],
                                                     so.h[2], so.gamma, so.gm1, so.small_pres));
   }
-  if (so.bits) block_max_to(smax_lane, so.bits);
+  if (so.dt) block_speed_to(smax_lane, so.dt, so.cfl);
 }
 
 // O9 + O10 fused, streamed along z: a workgroup owns an x-y tile of
@@ -1301,7 +1313,7 @@ __global__ void __launch_bounds__(STREAM_MAX_THREADS) k_final_stream(
       update_zone(uo, df, sc, grav, g0, g1, g2, un);
 #pragma unroll
       for (int m = 0; m < 5; ++m) Unew[ui + m * NS] = un[m];
-      if (so.bits)
+      if (so.dt)
         smax_lane = smax(smax_lane, fold_signal_speed(0.0, un[0], un[1], un[2], un[3], un[4], so.h[0], so.h[1],
                                                       so.h[2], so.gamma, so.gm1, so.small_pres));
     }
@@ -1311,7 +1323,7 @@ __global__ void __launch_bounds__(STREAM_MAX_THREADS) k_final_stream(
     __syncthreads();  // before the next plane's faces overwrite the LDS
   }
   raise_flags(flags, fl);
-  if (so.bits) block_max_to(smax_lane, so.bits);
+  if (so.dt) block_speed_to(smax_lane, so.dt, so.cfl);
 }
 
 // O11: max over valid zones and axes of (|u_d| + c)/h_d, FP64.  A fixed grid
@@ -1325,7 +1337,7 @@ __global__ void __launch_bounds__(MAX_TILE) k_wavespeed(const Tile* __restrict__
                                                     const double* __restrict__ U, double h0, double h1,
                                                     double h2, double gamma, double gm1,
                                                     double small_pres,
-                                                    unsigned long long* __restrict__ smax_bits) {
+                                                    double* dt, double cfl) {
   double s = 0.0;
   for (int tt = blockIdx.x; tt < ntiles; tt += gridDim.x) {
     const Tile tl = tiles[tt];
@@ -1339,19 +1351,11 @@ __global__ void __launch_bounds__(MAX_TILE) k_wavespeed(const Tile* __restrict__
       s = fold_signal_speed(s, u[0], u[NS], u[2 * NS], u[3 * NS], u[4 * NS], h0, h1, h2, gamma, gm1, small_pres);
     }
   }
-  block_max_to(s, smax_bits);
+  block_speed_to(s, dt, cfl);
 }
 
-__global__ void __launch_bounds__(64) k_zero_u64(unsigned long long* p) {
-  if (threadIdx.x == 0) p[0] = 0ull;
-}
-
-__global__ void __launch_bounds__(64) k_finish_dt(double* dt_dev, double cfl) {
-  if (threadIdx.x == 0) {
-    const double s = __longlong_as_double((long long)(((unsigned long long*)dt_dev)[1]));
-    dt_dev[1] = s;
-    dt_dev[0] = cfl / s;
-  }
+__global__ void __launch_bounds__(64) k_clear_speed(double* dt) {
+  if (threadIdx.x == 0) clear_speed(dt);
 }
 
 // O1: ghost fill over the plan.  One lane per destination ghost zone.  A
@@ -1536,13 +1540,11 @@ hipError_t launch_fill(const DevLevel& L, double* U, int desc_begin, int desc_en
 hipError_t launch_compute_dt(const DevLevel& L, int tile_begin, int tile_end, const double* U,
                              const double h[3], double gamma, double small_pres, double cfl,
                              double* dt_dev, hipStream_t s) {
-  unsigned long long* bits = (unsigned long long*)(dt_dev + 1);
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, bits);
+  hipLaunchKernelGGL(k_clear_speed, dim3(1), dim3(64), 0, s, dt_dev);
   const int n = tile_end - tile_begin;
   if (n > 0)
     hipLaunchKernelGGL(k_wavespeed, dim3(n < 2048 ? n : 2048), dim3(L.tile), 0, s, L.tilesE + tile_begin, n, L.boxes, U,
-                       h[0], h[1], h[2], gamma, gamma - 1.0, small_pres, bits);
-  hipLaunchKernelGGL(k_finish_dt, dim3(1), dim3(64), 0, s, dt_dev, cfl);
+                       h[0], h[1], h[2], gamma, gamma - 1.0, small_pres, dt_dev, cfl);
   return hipGetLastError();
 }
 
@@ -1559,11 +1561,6 @@ hipError_t launch_step(const DevLevel& L, int precision, int tS0, int tS1, int t
   return step_impl<double>(L, tS0, tS1, tE0, tE1, tB0, tB1, tF0, tF1, fr, U, Unew, flux, work,
                            make_gas<double>(gamma, small_dens, small_pres, limiter, flattening, iters, grav),
                            g, s, ev, upto, so, st);
-}
-
-hipError_t launch_speed_finish(double* dt_dev, double cfl, hipStream_t s) {
-  hipLaunchKernelGGL(k_finish_dt, dim3(1), dim3(64), 0, s, dt_dev, cfl);
-  return hipGetLastError();
 }
 
 }  // namespace ppm

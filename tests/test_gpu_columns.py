@@ -112,3 +112,21 @@ def test_front_end_in_one_launch_agrees_bitwise(tiling, precision):
             assert torch.equal(a, b), (tiling, precision, mode)
         for a, b in zip(ref[3], got[3]):
             assert torch.equal(a, b), (tiling, precision, mode)
+
+
+def test_time_step_of_a_state_without_a_speed():
+    """Speeds that are not numbers are left out of the time step; with no other
+    the largest speed is 0 and any step is allowed."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lay, h, U, p = _level(([5, 4], [4], [20]), 0)
+    lev = P.Level(lay)
+    dt = lev.compute_dt(U, h, p).clone()
+    assert dt[0].item() > 0 and dt[0].item() == p.cfl / dt[1].item()
+    nan = torch.full_like(U, float("nan"))
+    pair = dt.clone()
+    for _ in range(2):
+        lev.compute_dt(nan, h, p, out=pair)
+        assert pair[0] == float("inf") and pair[1] == 0
+    lev.compute_dt(U, h, p, out=pair)
+    assert torch.equal(pair, dt)
