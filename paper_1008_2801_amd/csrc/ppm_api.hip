@@ -813,7 +813,7 @@ static int hydro_step_impl(ppm_ctx* ctx, const double* U, double* Unew, double* 
   hipStream_t s = (hipStream_t)stream;
   const DevLevel L = ctx->level();
   int rc = PPM_OK;
-  const SpeedOut so{dt_next, params->cfl, {dx[0], dx[1], dx[2]}, params->gamma, params->gamma - 1.0,
+  const SpeedOut so{dt_next, L.consts->speed, params->cfl, {dx[0], dx[1], dx[2]}, params->gamma, params->gamma - 1.0,
                     params->small_pres};
   StepStart st = step_start(dt, dt_dev, dx, params, dt_next);
   const int grav = (params->grav[0] != 0.0 || params->grav[1] != 0.0 || params->grav[2] != 0.0) ? 1 : 0;

@@ -131,11 +131,15 @@ inline __host__ __device__ int inv_axis_class(int y, int n) { return (y < NG ? 1
 
 // Per-step constants formed on the device from dt (so that a graph can take
 // dt from device memory).  The reconstruction copies exist in FP64 and FP32.
+constexpr int SPEED_SLOTS = 16;
 struct StepConsts {
   double dt, hdt;
   double dtdx[3];
   double d_dtdx[3], d_dt2h[3], d_dt3h[3], d_hdtg[3];
   float f_dtdx[3], f_dt2h[3], f_dt3h[3], f_hdtg[3];
+  // largest speed of the update's workgroups by index modulo the slots, a cache
+  // line each (the bits of non-negative doubles)
+  alignas(128) unsigned long long speed[SPEED_SLOTS][16];
 };
 
 // Number of planes in the traced-grid (E) arena: flattening 1, traces 30,
@@ -208,6 +212,7 @@ enum { STEP_TO_STAGE2 = 5, STEP_FULL = 7, STEP_FULL_STAGED = 8 };
 // dt[0] = cfl / dt[1].
 struct SpeedOut {
   double* dt;
+  unsigned long long (*slots)[16];  // StepConsts::speed
   double cfl;
   double h[3];
   double gamma, gm1, small_pres;

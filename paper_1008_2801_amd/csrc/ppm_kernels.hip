@@ -122,6 +122,7 @@ __global__ void __launch_bounds__(MAX_TILE) k_prim(const Tile* __restrict__ tile
       step_consts(consts, st.dt, st.dt_dev, st.h[0], st.h[1], st.h[2], st.g[0], st.g[1], st.g[2]);
       if (st.dt_next) clear_speed(st.dt_next);  // after dt was read, which may be the same
     }
+    if (threadIdx.x < SPEED_SLOTS) consts->speed[threadIdx.x][0] = 0ull;
     return;
   }
   prim_body(xcd_tile(ntiles), tiles, boxes, U, prim, LS, G, flags);
@@ -844,8 +845,13 @@ __device__ __forceinline__ double fold_signal_speed(double s, double r, double m
 // divide after them.  The bits of non-negative doubles order like the doubles:
 // a maximum of integers per workgroup, skipped when the running maximum is
 // already as large, and a minimum only from those that raised it (one from each
-// costs a 256 x 256 x 4 step 7 us).  Every lane of the workgroup must call it.
-__device__ __forceinline__ void block_speed_to(double s, double* dt, double cfl) {
+// costs a 256 x 256 x 4 step 7 us).  On a level that the chip holds at once all
+// workgroups come here together, before any has raised the maximum, and queue
+// at its address: slots (the workgroups by index, and so by XCD) each let only
+// the workgroups pass that raise the slot's own maximum (256 x 256 x 4: k_update
+// 25.1 -> 14.5 us, 64^3: 19.6 -> 12.8).  Every lane of the workgroup must call it.
+__device__ __forceinline__ void block_speed_to(double s, double* dt, double cfl,
+                                               unsigned long long (*slots)[16] = nullptr) {
   for (int off = 32; off > 0; off >>= 1) s = smax(s, __shfl_xor(s, off, 64));
   __shared__ double wmax[MAX_TILE / 64];
   if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = s;
@@ -855,6 +861,10 @@ __device__ __forceinline__ void block_speed_to(double s, double* dt, double cfl)
     for (int w = 1; w < (int)(blockDim.x / 64); ++w) m = smax(m, wmax[w]);
     const unsigned long long mb = (unsigned long long)__double_as_longlong(m);
     unsigned long long* bits = (unsigned long long*)dt;
+    if (slots) {
+      unsigned long long* slot = slots[blockIdx.x % SPEED_SLOTS];
+      if (mb <= __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || mb <= atomicMax(slot, mb)) return;
+    }
     if (mb > __hip_atomic_load(bits + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) && mb > atomicMax(bits + 1, mb))
       atomicMin(bits, (unsigned long long)__double_as_longlong(cfl / m));
   }
@@ -921,7 +931,7 @@ __global__ void __launch_bounds__(MAX_TILE) k_update(const Tile* __restrict__ ti
   const int tt = xcd_tile(ntiles);
   if (tt < 0) return;  // the whole workgroup
   const double smax_lane = update_tile(tt, tiles, boxes, U, Unew, work, LE, sc, grav, g0, g1, g2, so);
-  if (so.dt) block_speed_to(smax_lane, so.dt, so.cfl);
+  if (so.dt) block_speed_to(smax_lane, so.dt, so.cfl, so.slots);
 }
 
 
@@ -1123,7 +1133,7 @@ k_final_columns(const Column* __restrict__ cols, int ncols, const DevBox* __rest
     for (int m = 0; m < 5; ++m) fzl[m] = F[m];
   }
   raise_flags(flags, (zone ? flz : 0) | (face ? flx : 0));
-  if (so.dt) block_speed_to(s, so.dt, so.cfl);
+  if (so.dt) block_speed_to(s, so.dt, so.cfl, so.slots);
 }
 
 // O9 + O10 fused on a brick of valid zones: the final fluxes of every face
@@ -1206,7 +1216,7 @@ __global__ void __launch_bounds__(BRICK_THREADS) k_final_update(const Brick* __r
       smax_lane = smax(smax_lane, fold_signal_speed(0.0, un[0], un[1], un[2], un[3], un[4], so.h[0], so.h[1],
                                                     so.h[2], so.gamma, so.gm1, so.small_pres));
   }
-  if (so.dt) block_speed_to(smax_lane, so.dt, so.cfl);
+  if (so.dt) block_speed_to(smax_lane, so.dt, so.cfl, so.slots);
 }
 
 // O9 + O10 fused, streamed along z: a workgroup owns an x-y tile of
@@ -1323,7 +1333,7 @@ __global__ void __launch_bounds__(STREAM_MAX_THREADS) k_final_stream(
     __syncthreads();  // before the next plane's faces overwrite the LDS
   }
   raise_flags(flags, fl);
-  if (so.dt) block_speed_to(smax_lane, so.dt, so.cfl);
+  if (so.dt) block_speed_to(smax_lane, so.dt, so.cfl, so.slots);
 }
 
 // O11: max over valid zones and axes of (|u_d| + c)/h_d, FP64.  A fixed grid
