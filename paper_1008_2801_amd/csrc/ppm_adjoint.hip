@@ -519,6 +519,16 @@ __global__ void __launch_bounds__(XF_THREADS) k_adj_r2_x(const Tile* __restrict_
   }
   prim_to_cons(qeL, G, ue0L);
   prim_to_cons(qeR, G, ue0R);
+  // the stage-3 part, loaded ahead of the solves: behind them, two waves per
+  // SIMD wait for every load (128^3 FP64 338 -> 285 us)
+  S t3L[5] = {0, 0, 0, 0, 0}, t3R[5] = {0, 0, 0, 0, 0};
+  if (own && (va || vb)) {
+#pragma unroll
+    for (int m = 0; m < 5; ++m) {
+      t3L[m] = a[(A_TB + m) * LE - 1];
+      t3R[m] = a[(A_TB + 5 + m) * LE];
+    }
+  }
   S tLb[5] = {0, 0, 0, 0, 0}, tRb[5] = {0, 0, 0, 0, 0};
   // one pair's corrected-state adjoints -> each owned zone's sum of sides
   auto sides = [&](int pr, bool hi_ok, bool lo_ok, const S uL[5], const S uR[5]) {
@@ -548,8 +558,8 @@ __global__ void __launch_bounds__(XF_THREADS) k_adj_r2_x(const Tile* __restrict_
   if (own && (va || vb)) {
 #pragma unroll
     for (int m = 0; m < 5; ++m) {
-      a[(A_TB + m) * LE - 1] += tLb[m];
-      a[(A_TB + 5 + m) * LE] += tRb[m];
+      a[(A_TB + m) * LE - 1] = t3L[m] + tLb[m];
+      a[(A_TB + 5 + m) * LE] = t3R[m] + tRb[m];
     }
   }
 }
@@ -596,20 +606,28 @@ __device__ __forceinline__ void adj_r1_body(const Tile* __restrict__ tiles, int 
     L[m] = w[(E_TRACE + (d * 2 + 0) * 5 + m) * LE - sd];
     R[m] = w[(E_TRACE + (d * 2 + 1) * 5 + m) * LE];
   }
+  // what the earlier stages left, loaded ahead of the solve: behind it, two or
+  // three waves per SIMD wait for every load (128^3 FP64 380 -> 360 us)
+  S tL[5], tR[5];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    tL[m] = a[(A_TB + (d * 2 + 0) * 5 + m) * LE - sd];
+    tR[m] = a[(A_TB + (d * 2 + 1) * 5 + m) * LE];
+  }
   const int ws = wall_states<d>(B, z.x[d], L, R);
   S Lb[5] = {0, 0, 0, 0, 0}, Rb[5] = {0, 0, 0, 0, 0};
   riemann_vjp<d>(L, R, G, Fb, Lb, Rb);
   wall_states_vjp<d>(ws, Lb, Rb);
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    a[(A_TB + (d * 2 + 0) * 5 + m) * LE - sd] += Lb[m];
-    a[(A_TB + (d * 2 + 1) * 5 + m) * LE] += Rb[m];
+    a[(A_TB + (d * 2 + 0) * 5 + m) * LE - sd] = tL[m] + Lb[m];
+    a[(A_TB + (d * 2 + 1) * 5 + m) * LE] = tR[m] + Rb[m];
   }
 }
 
 // Axes y and z (blockIdx.y 0, 1); x runs in k_adj_r1_trace_x.
 template <class S>
-__global__ void __launch_bounds__(MAX_TILE) k_adj_r1(const Tile* __restrict__ tiles, int ntiles,
+__global__ void __launch_bounds__(MAX_TILE) __attribute__((amdgpu_waves_per_eu(3))) k_adj_r1(const Tile* __restrict__ tiles, int ntiles,
                                                  const DevBox* __restrict__ boxes, const S* __restrict__ work,
                                                  long long LE, S* __restrict__ aw, Gas<S> G,
                                                  const StepConsts* __restrict__ sc) {
@@ -628,7 +646,7 @@ __global__ void __launch_bounds__(MAX_TILE) k_adj_r1(const Tile* __restrict__ ti
 // the zone's traced-state adjoint of field m on that side.  act false:
 // no memory is touched and out receives zeros (the lane still calls out,
 // which may hold workgroup barriers).
-template <int d, class S, class TB, class Out>
+template <int d, bool RELOAD, class S, class TB, class Out>
 __device__ __forceinline__ void trace_reverse_zone(bool act, const S* __restrict__ prim, long long LS,
                                                    long long base, long long st, S phi, TB&& tbv,
                                                    const Gas<S>& G, S dtdx, S& cb_out, S& phib_out,
@@ -641,13 +659,19 @@ __device__ __forceinline__ void trace_reverse_zone(bool act, const S* __restrict
     c = sound_speed(prim[base], prim[4 * LS + base], G);
   }
   S phib = 0;
-  // one field's parabola adjoint -> its stencil contributions (the stencil
-  // reloaded through an opaque address, so that the first loads' registers
-  // do not stay live in between)
+  auto address = [&](int m) -> const S* {
+    const S* p = prim + m * LS + base;
+    if constexpr (RELOAD) p = opaque(p);
+    return p;
+  };
+  // one field's parabola adjoint -> its stencil contributions (RELOAD: the
+  // stencil comes through an opaque address, so that the first loads' registers
+  // do not stay live in between, for kernels that would spill otherwise: y and
+  // z, 260 -> 480 us at 128^3 FP64 without; x is 4% faster without)
   auto contrib = [&](int m, S aLb, S aRb, S a6b, S centre) {
     S ab[5] = {0, 0, 0, 0, 0};
     if (act) {
-      const S* p = opaque(prim + m * LS + base);
+      const S* p = address(m);
       const S as5[5] = {p[-2 * st], p[-st], p[0], p[st], p[2 * st]};
       ppm_parabola_vjp(as5, phi, G, aLb, aRb, a6b, ab, phib);
       ab[2] += centre;
@@ -660,13 +684,16 @@ __device__ __forceinline__ void trace_reverse_zone(bool act, const S* __restrict
   for (int i = 0; i < 2; ++i) {
     const int m = (i == 0) ? 1 + t1 : 1 + t2;
     S aLb = 0, aRb = 0, a6b = 0;
+    S ab[5] = {0, 0, 0, 0, 0};
     if (act) {
-      const S* p = opaque(prim + m * LS + base);
+      const S* p = address(m);
+      const S as5[5] = {p[-2 * st], p[-st], p[0], p[st], p[2 * st]};
       S aL, aR, a6;
-      ppm_parabola(p[-2 * st], p[-st], p[0], p[st], p[2 * st], phi, G, aL, aR, a6);
+      ppm_parabola(as5[0], as5[1], as5[2], as5[3], as5[4], phi, G, aL, aR, a6);
       trace_transverse_vjp(aL, aR, a6, un, c, dtdx, tbv(0, m), tbv(1, m), aLb, aRb, a6b, lambt);
+      ppm_parabola_vjp(as5, phi, G, aLb, aRb, a6b, ab, phib);
     }
-    contrib(m, aLb, aRb, a6b, S(0));
+    out(m, ab);
   }
   // then density, normal velocity and pressure together
   S aL[5], aR[5], a6[5], qpb[5], qmb[5];
@@ -675,7 +702,7 @@ __device__ __forceinline__ void trace_reverse_zone(bool act, const S* __restrict
     const int m = fm[i];
     aL[m] = aR[m] = a6[m] = qpb[m] = qmb[m] = S(0);
     if (act) {
-      const S* p = opaque(prim + m * LS + base);
+      const S* p = address(m);
       ppm_parabola(p[-2 * st], p[-st], p[0], p[st], p[2 * st], phi, G, aL[m], aR[m], a6[m]);
       qpb[m] = tbv(0, m);
       qmb[m] = tbv(1, m);
@@ -719,7 +746,7 @@ k_adj_trace(const Tile* __restrict__ tiles, int ntiles, const DevBox* __restrict
   const S phi = work[E_FLAT * LE + B.eoff + z.e];
   S* a = aw + B.eoff + z.e;
   S cb, phib;
-  trace_reverse_zone<d>(true, prim, LS, base, st, phi,
+  trace_reverse_zone<d, true>(true, prim, LS, base, st, phi,
                         [&](int side, int m) { return a[(A_TB + (d * 2 + side) * 5 + m) * LE]; }, G,
                         SC<S>::dtdx(sc)[d], cb, phib, [&](int m, const S ab[5]) {
 #pragma unroll
@@ -772,6 +799,12 @@ k_adj_r1_trace_x(const Tile* __restrict__ tiles, int ntiles, const DevBox* __res
   // zone i low side)
   const bool face = slot && x >= 0;
   S Lb[5] = {0, 0, 0, 0, 0}, Rb[5] = {0, 0, 0, 0, 0};
+  S qp[5], qm[5];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    qp[m] = act ? a[(A_TB + m) * LE] : S(0);
+    qm[m] = act ? a[(A_TB + 5 + m) * LE] : S(0);
+  }
   if (face) {
     const S c3 = SC<S>::dt3h(sc)[0];
     S Fb[5];
@@ -799,21 +832,19 @@ k_adj_r1_trace_x(const Tile* __restrict__ tiles, int ntiles, const DevBox* __res
   for (int m = 0; m < 5; ++m) buf[m][l] = Lb[m];
   __syncthreads();
   // the zone's traced-state adjoints, complete
-  S qp[5] = {0, 0, 0, 0, 0}, qm[5] = {0, 0, 0, 0, 0};
   if (act) {
     const bool up = x + 1 <= B.n[0];  // the face above the zone is in its row
 #pragma unroll
     for (int m = 0; m < 5; ++m) {
-      const S p0 = a[(A_TB + m) * LE], m0 = a[(A_TB + 5 + m) * LE];
-      qp[m] = up ? p0 + buf[m][l + 1] : p0;
-      qm[m] = face ? m0 + Rb[m] : m0;
+      if (up) qp[m] += buf[m][l + 1];
+      if (face) qm[m] += Rb[m];
     }
   }
   __syncthreads();
   const long long base = act ? pidx(B, x, y, zz) : 0;
   const S phi = act ? work[E_FLAT * LE + B.eoff + i] : S(0);
   S cb, phib;
-  trace_reverse_zone<0>(act, prim, LS, base, 1, phi, [&](int side, int m) { return side == 0 ? qp[m] : qm[m]; },
+  trace_reverse_zone<0, false>(act, prim, LS, base, 1, phi, [&](int side, int m) { return side == 0 ? qp[m] : qm[m]; },
                         G, SC<S>::dtdx(sc)[0], cb, phib, [&](int m, const S ab[5]) {
 #pragma unroll
                           for (int o = 0; o < 5; ++o) buf[o][l] = ab[o];
@@ -939,8 +970,11 @@ __global__ void __launch_bounds__(MAX_TILE) k_adj_flatten(const Tile* __restrict
       sel = dsel;
     }
   }
+  // the gather reads the contributions of the selected axis only
+  if (sel >= 0) {
 #pragma unroll
-  for (int k = 0; k < 7; ++k) a[(A_GF + k) * LE] = gf[k];
+    for (int k = 0; k < 7; ++k) a[(A_GF + k) * LE] = gf[k];
+  }
   a[A_SEL * LE] = (S)sel;
 }
 
