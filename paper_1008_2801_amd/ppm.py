@@ -771,9 +771,11 @@ def _autograd():
                 if k % every == 0:
                     ckpts[k] = U.clone()
                 level.fill_boundary(U)
-                if dts_in is None:
-                    level.compute_dt(U, dx, p, out=dts[k])
-                level.hydro_step(U, V, dx, p, dt_dev=dts[k])
+                # each step leaves the next one's dt: no pass of its own over the state
+                if dts_in is None and k == 0:
+                    level.compute_dt(U, dx, p, out=dts[0])
+                nxt = dts[k + 1] if dts_in is None and k + 1 < nsteps else None
+                level.hydro_step(U, V, dx, p, dt_dev=dts[k], dt_next=nxt)
                 U, V = V, U
             ctx.level, ctx.nsteps, ctx.dx, ctx.p, ctx.every = level, nsteps, dx, p, every
             ctx.ckpts, ctx.dts, ctx.saved = ckpts, dts, saved
@@ -791,11 +793,11 @@ def _autograd():
             if saved is None:  # keep one workspace per segment step if it fits in half the free memory
                 free, _ = torch.cuda.mem_get_info(g.device)
                 saved = m * (lev.workspace_bytes(prec) + 256) <= free // 2
-            # the filled input states of one segment; without saved
-            # workspaces the segment's last step is not replayed (its output
-            # is not needed), with them every step runs on its own workspace
+            # the filled input states of one segment; its last step is not
+            # replayed (its output is not needed, and its adjoint runs the
+            # stages it reads itself), with saved workspaces the others run
+            # each on its own
             slots = [torch.empty_like(g) for _ in range(m)]
-            scratch = torch.empty_like(g) if saved else None
             try:
                 for s0 in reversed(range(0, n, every)):
                     s1 = min(n, s0 + every)
@@ -804,14 +806,13 @@ def _autograd():
                         lev.fill_boundary(slots[k - s0])
                         if saved:
                             lev.select_workspace(k - s0, prec)
-                            out = slots[k + 1 - s0] if k + 1 < s1 else scratch
-                            lev.hydro_step(slots[k - s0], out, ctx.dx, ctx.p, dt_dev=ctx.dts[k])
-                        elif k + 1 < s1:
+                        if k + 1 < s1:
                             lev.hydro_step(slots[k - s0], slots[k + 1 - s0], ctx.dx, ctx.p, dt_dev=ctx.dts[k])
                     for k in reversed(range(s0, s1)):
                         if saved:
                             lev.select_workspace(k - s0, prec)
-                        lev.hydro_step_adjoint(slots[k - s0], g, Ub, ctx.dx, ctx.p, dt_dev=ctx.dts[k], saved=saved)
+                        lev.hydro_step_adjoint(slots[k - s0], g, Ub, ctx.dx, ctx.p, dt_dev=ctx.dts[k],
+                                               saved=saved and k + 1 < s1)
                         g, Ub = Ub, g
             finally:
                 if saved:
