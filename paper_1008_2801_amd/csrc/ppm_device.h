@@ -85,7 +85,21 @@ inline Gas<S> make_gas(double gamma, double small_dens, double small_pres, int l
   G.flattening = flattening && limiter;
   G.iters = iters;
   G.grav = grav;
+  G.resident = G.prim_resident = 0;
   return G;
+}
+
+// Store to a plane that a later stage reads: with the streaming hint, so that
+// the lines this stage still reads stay in L2, or plainly on a level where the
+// caches hold the plane until then (as a relaxed store of the wave's own scope,
+// the same instruction as a plain one: two plain stores would be merged into
+// one without the hint).
+template <class S>
+__device__ __forceinline__ void store_plane(S v, S* p, int resident) {
+  if (resident)
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  else
+    __builtin_nontemporal_store(v, p);
 }
 
 // Riemann problem on a reflecting wall: the state outside the wall is the

@@ -101,11 +101,11 @@ __device__ __forceinline__ void prim_body(int t, const Tile* __restrict__ tiles,
         speed_in_range(vz)))
     fl |= PPM_FLAG_RANGE;
   S* q = prim + B.poff + idx;
-  __builtin_nontemporal_store(r, &q[0]);
-  __builtin_nontemporal_store(vx, &q[LS]);
-  __builtin_nontemporal_store(vy, &q[2 * LS]);
-  __builtin_nontemporal_store(vz, &q[3 * LS]);
-  __builtin_nontemporal_store(p, &q[4 * LS]);
+  store_plane(r, &q[0], G.prim_resident);
+  store_plane(vx, &q[LS], G.prim_resident);
+  store_plane(vy, &q[2 * LS], G.prim_resident);
+  store_plane(vz, &q[3 * LS], G.prim_resident);
+  store_plane(p, &q[4 * LS], G.prim_resident);
   raise_flags(flags, fl);
 }
 
@@ -278,7 +278,7 @@ __device__ __forceinline__ void stage1_face(const DevBox& B, int xd, S L[5], S R
   riemann<d>(L, R, G, F, fl);
   S* f = work + B.eoff + e;
 #pragma unroll
-  for (int m = 0; m < 5; ++m) __builtin_nontemporal_store(F[m], &f[(E_F1 + d * 5 + m) * LE]);
+  for (int m = 0; m < 5; ++m) store_plane(F[m], &f[(E_F1 + d * 5 + m) * LE], G.resident);
 }
 
 // O7: F^d at d-face slots x_d in [0, n], transverse in [-1, n].
@@ -658,7 +658,7 @@ __device__ __forceinline__ void riemann2_pair(const S* __restrict__ w, S* __rest
   S F[5];
   riemann<d>(L, R, G, F, fl);
 #pragma unroll
-  for (int m = 0; m < 5; ++m) __builtin_nontemporal_store(F[m], &o[(E_F2 + pr * 5 + m) * LE]);
+  for (int m = 0; m < 5; ++m) store_plane(F[m], &o[(E_F2 + pr * 5 + m) * LE], G.resident);
 }
 
 template <int d, class S>
@@ -1426,6 +1426,23 @@ __global__ void __launch_bounds__(FILL_THREADS) k_fill(const FillDesc* __restric
 }
 
 
+// Whether the flux planes are stored without the streaming hint: in FP64 where
+// the planes that the stages hand on (traces and fluxes, 75 of them) fit in the
+// 256 MB Infinity Cache.  k_riemann2 + k_riemann3, with -> without (us): 48^3
+// 39.4 -> 35.7, 64^3 76.2 -> 69.2, 256 x 256 x 4 (3.2 MB a plane) 87.8 -> 82.8;
+// without it 80^3 (4.4 MB) goes from 140 to 150, 96^3 from 249 to 274.  FP32
+// gains nowhere (64^3 52 -> 53, 96^3 146 -> 150).
+template <class S> bool planes_resident(long long LE) {
+  return sizeof(S) == 8 && 80 * LE * (long long)sizeof(S) <= (256ll << 20);
+}
+
+// Whether the primitives are: where their five planes fill at most a quarter of
+// it.  k_prim, k_flatten, k_front_x and k_trace, with -> without (us): 256 x 256
+// x 4 71.0 -> 67.7, 80^3 86.6 -> 82.0, FP32 96^3 85.6 -> 80.0, FP32 128^3 175 ->
+// 168, 96^3 (45 MB) 160 -> 157; 128^3 (100 MB), where the columns follow: 415 ->
+// 413, and 8 boxes of 64^3 (120 MB) 392 -> 396.
+template <class S> bool prim_resident(long long LS) { return 5 * LS * (long long)sizeof(S) <= (64ll << 20); }
+
 template <class S>
 hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int tB0, int tB1, int tF0, int tF1,
                      const FrontRanges& fr, const double* U,
@@ -1437,6 +1454,8 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
   const Tile* TS = L.tilesS + tS0;
   const Tile* TE = L.tilesE + tE0;
   if (nS <= 0 || nE <= 0) return hipSuccess;
+  G.resident = planes_resident<S>(L.LE);
+  G.prim_resident = prim_resident<S>(L.LS);
   const dim3 blk(L.tile);
   if (ev) (void)hipEventRecord(ev[0], s);
   hipLaunchKernelGGL(k_prim<S>, dim3(xcd_grid(nS) + (st.on ? 1 : 0)), blk, 0, s, TS, nS, L.boxes, U, prim, L.LS, G,

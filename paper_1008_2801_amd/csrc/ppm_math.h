@@ -57,6 +57,7 @@ namespace ppm {
 template <class S> struct Gas {
   S gamma, gm1, gm1inv, beta, ombeta, small_dens, small_pres, ismall_dens;  // ombeta = 1 - beta
   int limiter, flattening, iters, grav;
+  int resident, prim_resident;  // the flux planes, the primitives stay in the caches until read (store_plane)
 };
 
 
