@@ -363,10 +363,11 @@ int ppm_graph_destroy(ppm_graph* g);
 int ppm_set_tiling(ppm_ctx* ctx, int32_t tile, int32_t strip_rows);
 int ppm_get_tiling(const ppm_ctx* ctx, int32_t* tile, int32_t* strip_rows);
 
-/* Form of the step's last stage.  fused = 0 (the default): the final
- * fluxes go to the workspace and a separate kernel updates the zones, or, on
- * large FP64 levels, one kernel whose lanes walk columns of zones along z does
- * both, the final fluxes kept in registers.
+/* Form of the step's last stage.  fused = 0 (the default): chosen by the
+ * level's size.  On small levels (and in FP32 on large boxes) the final fluxes
+ * go to the workspace and a separate kernel updates the zones; on large FP64
+ * boxes one kernel whose lanes walk columns of zones along z does both, the
+ * final fluxes kept in registers; otherwise the bricks of form 1 do.
  * fused = 1: the final fluxes of each brick of 32 x 4 x 4 valid zones are
  * computed into LDS and the brick is updated from them in the same kernel
  * (the fluxes on a brick's faces are computed by both bricks that share
@@ -375,7 +376,7 @@ int ppm_get_tiling(const ppm_ctx* ctx, int32_t* tile, int32_t* strip_rows);
  * its lanes solve every x and y face of the tile and each zone's high z
  * face once into LDS (the high z faces serve as the next plane's low ones),
  * then update the plane (only the faces shared with neighbouring tiles and
- * runs are solved twice).  In forms 1 and 2 nothing is written to the
+ * runs are solved twice).  In the fused forms nothing is written to the
  * workspace's final-flux planes.  Results are identical bit for bit in all
  * forms.  The species step always runs the staged form (it reads the final
  * mass fluxes from the workspace).  The autotuner picks among the forms and

@@ -126,6 +126,7 @@ struct ppm_ctx {
     L.desc = d_desc;
     L.desc_start = d_start;
     L.consts = d_consts;
+    L.nbox = layout.nbox;
     L.flags = d_flags;
     L.inv_start = d_inv_start;
     L.inv_idx = d_inv_idx;

@@ -163,6 +163,7 @@ struct InflowView {
 // Launch-side views of the context's device data.
 struct DevLevel {
   const DevBox* boxes;
+  int nbox;
   const Tile* tilesS;  // tiles over the stored grids
   const Tile* tilesE;  // tiles over the traced grids
   const Tile* tilesX;  // runs of XF_OWNED traced zones (front forms 2, 3)
@@ -180,7 +181,8 @@ struct DevLevel {
   int tile;            // zones per tile of the tile lists (threads per workgroup)
   InflowView inflow;
   const Brick* bricks;  // valid-zone blocks of every box (fused final stage)
-  int fused;            // 1: final fluxes and update in one brick kernel (fluxes kept in LDS);
+  int fused;            // 0: the final stage's form by rule (step_impl); 1: final fluxes and update in one
+                        // brick kernel (fluxes kept in LDS);
                         // 2: the same in x-y tiles streamed along z (ppm_kernels.hip, k_final_stream)
   int stream_e[3];      // form 2: x, y extents of a tile (threads = product) and the z run
   const Brick* fbricks; // traced-grid x-y tiles with z runs (streamed front end)

@@ -16,8 +16,10 @@
 // Fused forms of some stage pairs cut that traffic and give the same bits:
 // the front end (trace + riemann1) along x with the face states exchanged
 // by lane shuffles (k_front_x, the default), along y and z in columns with the
-// stencil in registers (k_front_yz, the default on large levels), or streamed along z through LDS (k_front_stream); the final
-// stage (riemann3 + update) in bricks (k_final_update) or streamed along z
+// stencil in registers (k_front_yz, the default on large levels), all three in
+// one launch on small levels (k_front_small), or streamed along z through LDS
+// (k_front_stream); the final stage (riemann3 + update) in columns along z
+// (k_final_columns), in bricks (k_final_update) or streamed along z
 // (k_final_stream), the final fluxes kept in LDS.
 //
 // Every formula is a C expression evaluated as written (no contraction:
@@ -985,11 +987,28 @@ __device__ __forceinline__ void pair_diff_x(const S* __restrict__ w, long long L
   for (int m = 0; m < 5; ++m) D[m] = lane_up(f[m]) - f[m];
 }
 
-// Used in FP64, where its runs fill the card twice over (a 160^3 box, 1.4 times,
-// takes 800 us against 741 staged) and its planes leave the Infinity Cache.
-// FP32 stays staged: 256^3 1.56 ms against 1.63-1.73 (boxes of 64^3 gain 8%,
-// boxes of 40^3 lose 9%).
-bool final_columns_pay(long long LE, int groups) { return columns_pay<double>(LE, groups) && groups >= 1536; }
+// Used in FP64 on boxes of 100^3 zones and more, where its runs fill the card
+// twice over (a 160^3 box, 1.4 times, takes 800 us against 741 staged) and its
+// planes leave the Infinity Cache.  Step in bricks -> columns (us): 256^3 7964
+// -> 7625, 8 boxes of 128^3 8062 -> 7928, 200^3 3768 -> 3752; but 64 boxes of
+// 64^3 8340 -> 8402, 216 of them 26934 -> 27715, 512 boxes of 32^3 8957 -> 9482:
+// a short box leaves more of its workgroups' lanes and runs unused.  FP32, 256^3:
+// 1.63-1.73 ms against 1.56 staged.  zones: per box, on average.
+bool final_columns_pay(long long LE, long long zones, int groups) {
+  return columns_pay<double>(LE, groups) && groups >= 1536 && zones >= 1000000;
+}
+
+// Whether the final stage runs in bricks where it does not run in columns: from
+// two workgroups per CU on, and in FP32 (half the planes, so less to save, and
+// bricks cut to a box's extent leave lanes unused) on boxes below 80^3 zones.
+// Step staged -> bricks (us): FP64 64^3 136 -> 131, 64 boxes of 16^3 187 -> 170,
+// 256 x 256 x 4 179 -> 165, 96^3 449 -> 425, 8 boxes of 64^3 1158 -> 1067, 160^3
+// 2008 -> 1914; with fewer bricks 48^3 (288) 78 -> 86, 100 x 50 x 30 (416) 94.5
+// -> 97.4.  FP32 64 boxes of 32^3 764 -> 708, 64 of 64^3 5600 -> 5372; but one
+// box of 112^3 417 -> 435, of 256^3 4804 -> 4853.
+template <class S> bool final_bricks_pay(long long zones, int bricks) {
+  return bricks >= 512 && (sizeof(S) == 8 || zones < 512000);
+}
 
 template <class S>
 __global__ void __launch_bounds__(COL_THREADS) __attribute__((amdgpu_waves_per_eu(3)))
@@ -1519,7 +1538,11 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
     if (ev) (void)hipEventRecord(ev[7], s);
     return hipGetLastError();
   }
-  if (L.fused == 1 && upto == STEP_FULL && nB > 0) {
+  const int nCol = fr.f1 - fr.f0;
+  const long long zones = L.LE / L.nbox;
+  const bool columns_last = L.fused == 0 && sizeof(S) == 8 && final_columns_pay(L.LE, zones, nCol);
+  const bool bricks = L.fused == 1 || (L.fused == 0 && !columns_last && final_bricks_pay<S>(zones, nB));
+  if (bricks && upto == STEP_FULL && nB > 0) {
     hipLaunchKernelGGL(k_final_update<S>, dim3(xcd_grid(nB)), dim3(BRICK_THREADS), 0, s, L.bricks + tB0, nB,
                        L.boxes, (const S*)ework, L.LE, G, L.consts, U, Unew, fx, fy, fz, G.grav, g[0], g[1], g[2],
                        so, L.flags);
@@ -1528,8 +1551,7 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
     return hipGetLastError();
   }
   if constexpr (sizeof(S) == 8) {
-    const int nCol = fr.f1 - fr.f0;
-    if (upto == STEP_FULL && final_columns_pay(L.LE, nCol)) {
+    if (columns_last && upto == STEP_FULL) {
       hipLaunchKernelGGL(k_final_columns<S>, dim3(xcd_grid(nCol)), dim3(COL_THREADS), 0, s, L.colsF + fr.f0, nCol,
                          L.boxes, (const S*)ework, L.LE, G, L.consts, U, Unew, fx, fy, fz, G.grav, g[0], g[1], g[2],
                          so, L.flags);

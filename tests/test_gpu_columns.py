@@ -162,3 +162,21 @@ def test_plain_and_streaming_stores_agree_bitwise(n, precision):
         outs.append([V[b * lay.box_size(0):(b + 1) * lay.box_size(0)] for b in range(copies)])
     for b in range(2):
         assert torch.equal(outs[0][0], outs[1][b]), (n, precision, b)
+
+
+# boxes of a million zones in columns with several boxes; 511, 512 and more
+# bricks (32 x 4 x 4); FP32 boxes below and above 80^3 zones
+@pytest.mark.parametrize("tiling,precision", [(([200, 120], [150], [131, 60]), 0), (([32 * 7], [4 * 73], [4]), 0),
+                                              (([64], [64], [64]), 0), (([31, 5], [41, 40], [33, 50]), 0),
+                                              (([64], [64], [64]), 1), (([81], [81], [82]), 1)])
+def test_final_stage_by_rule_agrees_bitwise(tiling, precision):
+    """The form the rule takes (form 0) against the streamed form."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lay, h, U, p = _level(tiling, precision)
+    ref = _step(lay, h, U, p, P.BATCHED, 0, form=2)
+    got = _step(lay, h, U, p, P.BATCHED, 2)
+    for a, b in zip(ref[:3], got[:3]):
+        assert torch.equal(a, b), tiling
+    for a, b in zip(ref[3], got[3]):
+        assert torch.equal(a, b), tiling
