@@ -806,9 +806,12 @@ def roofline(wname, lay, prof, ms_step, precision, tiling):
     # riemann3 and update work, timed in the riemann3 slot.  The fused front
     # ends are timed in the trace slot: form 2 (x fused) holds the x axis's
     # riemann1 work there, the riemann1 slot the y and z axes'; forms 1 and 3
-    # hold all of it there
-    fused = len(tiling) > 2 and tiling[2] != 0
+    # hold all of it there.  Form 0 of either picks a fused kernel by the
+    # level's size: the slot it leaves is empty but for its two events
+    fused = (len(tiling) > 2 and tiling[2] != 0) or 0 < prof["update"][0] < 0.05 * prof["riemann3"][0]
     front = tiling[3] if len(tiling) > 3 else 0
+    if front == 2 and 0 < prof["riemann1"][0] < 0.05 * prof["trace"][0]:
+        front = 3
     stages = {k: prof[k] for k in STAGES if not (fused and k == "update") and not (front in (1, 3) and k == "riemann1")}
     flops_of = {k: table[k] * units[k] for k in stages}
     if fused:
@@ -830,8 +833,9 @@ def roofline(wname, lay, prof, ms_step, precision, tiling):
     alg = algorithmic_bytes_per_step(lay)
     name = dom
     if fused and dom == "riemann3":
-        name = ("final_update (riemann3 + update, brick form)" if tiling[2] == 1 else
-                "final_stream (riemann3 + update, streamed form)")
+        name = {0: "riemann3 + update, bricks or columns by rule",
+                1: "final_update (riemann3 + update, brick form)",
+                2: "final_stream (riemann3 + update, streamed form)"}[tiling[2] if len(tiling) > 2 else 0]
     elif front and dom == "trace":
         name = f"trace slot ({FRONT_FORMS[front]} front end: its fused kernels and any staged trace)"
     elif front == 2 and dom == "riemann1":

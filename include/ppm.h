@@ -430,7 +430,7 @@ int ppm_get_front_tiling(const ppm_ctx* ctx, int32_t* sx, int32_t* sy, int32_t* 
  * (ppm_hydro_step_dt, the next dt left on the device; reps steps after one
  * warm-up, HIP events on the stream) from the filled state U into Unew for
  * every candidate tile size x strip height, keeps the fastest, then times
- * the final stage staged (form 0), in bricks (form 1) and streamed (form 2)
+ * the final stage by rule (form 0), in bricks (form 1) and streamed (form 2)
  * with several tile shapes and keeps the fastest, and appends the choice
  * to the JSON-lines
  * file cache_path (may be null) keyed by device architecture, precision

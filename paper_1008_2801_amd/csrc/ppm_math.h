@@ -109,7 +109,8 @@ PPM_HD double qdiv(double a, double b) {
 PPM_HD float qdiv(float a, float b) { return a / b; }
 
 // Square root of the two-shock wave-speed factor 1 + beta (p/p_s - 1),
-// which is at least 1 - beta > 0.  FP64 on the device: the core of the
+// which is at least 1 - beta > 0, in the FP32 solver; in FP64, whose solver
+// takes reciprocal roots instead, the core of sqrt_phys: the core of the
 // correctly rounded square root hipcc emits (hardware reciprocal square
 // root, one Newton-Raphson step on the root and the half reciprocal, two
 // residual corrections of the root), without the rescaling of arguments
