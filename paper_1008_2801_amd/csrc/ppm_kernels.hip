@@ -132,6 +132,35 @@ __global__ void __launch_bounds__(MAX_TILE) k_prim(const Tile* __restrict__ tile
 
 
 // O3 on the traced zones.
+// 1 - chi along one axis: p and u at offsets -2..2 along it; pp the centre's
+// pressure, st the axis's stride.  p at -3 and 3 is read only by a neighbour's
+// coefficient at a strong compression (a branch that, away from shocks, no lane
+// of a wave takes).
+template <class S>
+__device__ __forceinline__ S flatten_axis(const S p5[5], const S u[5], const S* pp, long long st, const Gas<S>& G) {
+  S p[7];
+#pragma unroll
+  for (int o = -2; o <= 2; ++o) p[o + 3] = p5[o + 2];
+  // shock-detector coefficient at offset o; the pressure ratio (one
+  // division) only where the zone is a strong compression
+  auto chit = [&](int o) -> S {
+    const S dp1 = p[o + 4] - p[o + 2];
+    const bool compress = (u[o + 1] - u[o + 3]) > S(0);
+    const bool strong = sabs(dp1) > C033 * smin(p[o + 4], p[o + 2]);
+    if (!(compress && strong)) return S(0);
+    if (o != 0) p[3 + 3 * o] = pp[3 * o * st];
+    const S dp2 = p[o + 5] - p[o + 1];
+    const S zeta = qdiv(sabs(dp1), smax(sabs(dp2), G.small_pres));
+    return smin(smax(TEN * (zeta - C075), S(0)), ONE);
+  };
+  const S dp1 = p[4] - p[2];
+  S chi;
+  if (dp1 > S(0)) chi = smax(chit(0), chit(-1));
+  else if (dp1 < S(0)) chi = smax(chit(0), chit(1));
+  else chi = smax(smax(chit(-1), chit(0)), chit(1));
+  return ONE - chi;
+}
+
 template <class S>
 __device__ __forceinline__ void flatten_body(int t, const Tile* __restrict__ tiles,
                                              const DevBox* __restrict__ boxes, const S* __restrict__ prim,
@@ -150,33 +179,13 @@ __device__ __forceinline__ void flatten_body(int t, const Tile* __restrict__ til
     for (int d = 0; d < 3; ++d) {
       const long long st = stride(NS, d);
       const S* uu = prim + (1 + d) * LS + base;
-      // p at offsets -2..2 and u at -2..2 (index offset + 3, offset + 2)
-      // are read here; p at -3 and 3 only by a neighbour's coefficient at a
-      // strong compression (a branch that, away from shocks, no lane of a
-      // wave takes)
-      S p[7], u[5];
+      S p[5], u[5];
 #pragma unroll
-      for (int o = -2; o <= 2; ++o) p[o + 3] = pp[o * st];
+      for (int o = -2; o <= 2; ++o) p[o + 2] = pp[o * st];
 #pragma unroll
       for (int o = -2; o <= 2; ++o) u[o + 2] = uu[o * st];
-      // shock-detector coefficient at offset o; the pressure ratio (one
-      // division) only where the zone is a strong compression
-      auto chit = [&](int o) -> S {
-        const S dp1 = p[o + 4] - p[o + 2];
-        const bool compress = (u[o + 1] - u[o + 3]) > S(0);
-        const bool strong = sabs(dp1) > C033 * smin(p[o + 4], p[o + 2]);
-        if (!(compress && strong)) return S(0);
-        if (o != 0) p[3 + 3 * o] = pp[3 * o * st];
-        const S dp2 = p[o + 5] - p[o + 1];
-        const S zeta = qdiv(sabs(dp1), smax(sabs(dp2), G.small_pres));
-        return smin(smax(TEN * (zeta - C075), S(0)), ONE);
-      };
-      const S dp1 = p[4] - p[2];
-      S chi;
-      if (dp1 > S(0)) chi = smax(chit(0), chit(-1));
-      else if (dp1 < S(0)) chi = smax(chit(0), chit(1));
-      else chi = smax(smax(chit(-1), chit(0)), chit(1));
-      phi = (d == 0) ? (ONE - chi) : smin(phi, ONE - chi);
+      const S f = flatten_axis(p, u, pp, st, G);
+      phi = (d == 0) ? f : smin(phi, f);
     }
   }
   work[E_FLAT * LE + B.eoff + z.e] = phi;
@@ -223,6 +232,47 @@ __device__ __forceinline__ void trace_at(const DevBox& B, int x, int y, int z, l
     for (int o = 0; o < 5; ++o) v[m][o] = a[(o - 2) * st];
   }
   trace_vals<d>(v, work[E_FLAT * LE + B.eoff + e], G, sc, qp, qm, fl);
+}
+
+// O3 + O4 + O5 along x for one zone: the flattening coefficient (handed back
+// in phi) from the stencil that the trace loads and the y and z neighbours.  A
+// flattening kernel of its own waits for its loads three quarters of the time
+// at 2.7 TB/s; here they run under the traces' arithmetic.  k_flatten +
+// k_front_x -> k_front_x (us; 110 registers in FP64, and held to 96 it spills
+// and takes 1304 on 256^3): 256^3 933 -> 902, FP32 701 -> 621, 216 boxes of 64^3
+// 3518 -> 2988, 512 boxes of 16 to 64 zones per edge 1200 -> 1042, 96^3 55.1 ->
+// 48.2, 256 x 256 x 4 28.5 -> 25.5, and a launch less.
+template <class S>
+__device__ __forceinline__ void flatten_trace_x(const DevBox& B, int x, int y, int z, const S* __restrict__ prim,
+                                                long long LS, const Gas<S>& G, const StepConsts* __restrict__ sc,
+                                                S qp[5], S qm[5], S& phi, int& fl) {
+  const int NS[3] = {B.n[0] + 2 * NG, B.n[1] + 2 * NG, B.n[2] + 2 * NG};
+  const long long base = pidx(B, x, y, z);
+  S v[5][5];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    const S* a = prim + m * LS + base;
+#pragma unroll
+    for (int o = 0; o < 5; ++o) v[m][o] = a[o - 2];
+  }
+  phi = ONE;
+  if (G.flattening) {
+    const S* pp = prim + 4 * LS + base;
+    S p[2][5], u[2][5];
+#pragma unroll
+    for (int d = 1; d < 3; ++d) {
+      const long long st = stride(NS, d);
+#pragma unroll
+      for (int o = 0; o < 5; ++o) {
+        p[d - 1][o] = o == 2 ? v[4][2] : pp[(o - 2) * st];
+        u[d - 1][o] = o == 2 ? v[1 + d][2] : prim[(1 + d) * LS + base + (o - 2) * st];
+      }
+    }
+    phi = flatten_axis(v[4], v[1], pp, 1ll, G);
+    phi = smin(phi, flatten_axis(p[0], u[0], pp, stride(NS, 1), G));
+    phi = smin(phi, flatten_axis(p[1], u[1], pp, stride(NS, 2), G));
+  }
+  trace_vals<0>(v, phi, G, sc, qp, qm, fl);
 }
 
 // Traced states of zone e along d into the workspace planes.
@@ -332,7 +382,8 @@ __global__ void __launch_bounds__(MAX_TILE) __attribute__((amdgpu_waves_per_eu(8
 // neighbour of every zone with x >= 0 (a zone at x = -1 solves no face).
 // Same arithmetic as trace_at and stage1_face, so the same bits as the
 // staged trace and riemann1 kernels along x.
-template <class S>
+// FLAT: the flattening coefficients too, for the kernels of the other axes.
+template <bool FLAT, class S>
 __device__ __forceinline__ void front_x_body(int t, const Tile* __restrict__ tiles,
                                              const DevBox* __restrict__ boxes, const S* __restrict__ prim,
                                              long long LS, S* __restrict__ work, long long LE, const Gas<S>& G,
@@ -351,7 +402,13 @@ __device__ __forceinline__ void front_x_body(int t, const Tile* __restrict__ til
   S qp[5], qm[5];
   int fl = 0;
   if (have) {
-    trace_at<0>(B, x, y, z, idx, prim, LS, work, LE, G, sc, qp, qm, fl);
+    if constexpr (FLAT) {
+      S phi;
+      flatten_trace_x(B, x, y, z, prim, LS, G, sc, qp, qm, phi, fl);
+      if (own) work[E_FLAT * LE + B.eoff + idx] = phi;
+    } else {
+      trace_at<0>(B, x, y, z, idx, prim, LS, work, LE, G, sc, qp, qm, fl);
+    }
     if (own) store_traced<0>(work, LE, B, idx, qp, qm);
   } else {
 #pragma unroll
@@ -369,7 +426,7 @@ __global__ void __launch_bounds__(XF_THREADS) k_front_x(const Tile* __restrict__
                                                     const DevBox* __restrict__ boxes, const S* __restrict__ prim,
                                                     long long LS, S* __restrict__ work, long long LE, Gas<S> G,
                                                     const StepConsts* __restrict__ sc, int* flags) {
-  front_x_body(xcd_tile(ntiles), tiles, boxes, prim, LS, work, LE, G, sc, flags);
+  front_x_body<true>(xcd_tile(ntiles), tiles, boxes, prim, LS, work, LE, G, sc, flags);
 }
 
 // O4 + O5 + O7 along d (y or z) for one zone per lane: the lane traces its
@@ -412,7 +469,7 @@ __global__ void __launch_bounds__(XF_THREADS) k_front_small(const Tile* __restri
   const int t = xcd_tile(nX + 2 * nE);
   if (t < 0) return;
   if (t < nX)
-    front_x_body(t, tilesX, boxes, prim, LS, work, LE, G, sc, flags);
+    front_x_body<false>(t, tilesX, boxes, prim, LS, work, LE, G, sc, flags);
   else if (t < nX + nE)
     front_zone_body<1>(t - nX, tilesE, boxes, prim, LS, work, LE, G, sc, flags);
   else
@@ -1480,9 +1537,14 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
   hipLaunchKernelGGL(k_prim<S>, dim3(xcd_grid(nS) + (st.on ? 1 : 0)), blk, 0, s, TS, nS, L.boxes, U, prim, L.LS, G,
                      L.flags, st, L.consts);
   if (ev) (void)hipEventRecord(ev[1], s);
-  hipLaunchKernelGGL(k_flatten<S>, dim3(xcd_grid(nE)), blk, 0, s, TE, nE, L.boxes, prim, L.LS, ework, L.LE, G);
-  if (ev) (void)hipEventRecord(ev[2], s);
+  const int nX = fr.x1 - fr.x0, nY = fr.y1 - fr.y0, nZ = fr.z1 - fr.z0;
   const int nF = tF1 - tF0;
+  const int d0 = (L.front >= 2 && nX > 0) ? 1 : 0;
+  const bool columns = d0 && nY + nZ > 0 && (L.front == 3 || columns_pay<S>(L.LE, nY + nZ));
+  const bool small = d0 && !columns && L.tile == XF_THREADS && front_small_pays(nX + 2 * nE);
+  if (!d0 || small)  // else k_front_x does it
+    hipLaunchKernelGGL(k_flatten<S>, dim3(xcd_grid(nE)), blk, 0, s, TE, nE, L.boxes, prim, L.LS, ework, L.LE, G);
+  if (ev) (void)hipEventRecord(ev[2], s);
   if (L.front == 1 && nF > 0) {
     // trace and stage-1 solves in one kernel (timed in the trace slot)
     const int mx = L.front_m[0], my = L.front_m[1];
@@ -1495,10 +1557,6 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
   } else {
     // front forms 2 and 3: the x axis's trace and solves in one kernel, y's and
     // z's in columns always (3) or where that pays (2) (timed in the trace slot)
-    const int nX = fr.x1 - fr.x0, nY = fr.y1 - fr.y0, nZ = fr.z1 - fr.z0;
-    const int d0 = (L.front >= 2 && nX > 0) ? 1 : 0;
-    const bool columns = d0 && nY + nZ > 0 && (L.front == 3 || columns_pay<S>(L.LE, nY + nZ));
-    const bool small = d0 && !columns && L.tile == XF_THREADS && front_small_pays(nX + 2 * nE);
     if (d0 && !small)
       hipLaunchKernelGGL(k_front_x<S>, dim3(xcd_grid(nX)), dim3(XF_THREADS), 0, s, L.tilesX + fr.x0, nX, L.boxes,
                          (const S*)prim, L.LS, ework, L.LE, G, L.consts, L.flags);
