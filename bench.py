@@ -822,6 +822,10 @@ def roofline(wname, lay, prof, ms_step, precision, tiling):
         ux = sum(stage_units_axis(lay.n(b), 0) for b in range(lay.nbox))
         flops_of["trace"] += table["riemann1"] * ux
         flops_of["riemann1"] -= table["riemann1"] * ux
+    if front >= 2 and 0 < prof["flatten"][0] < 0.01 * prof["trace"][0]:
+        # the x front end forms the flattening coefficients
+        stages.pop("flatten")
+        flops_of["trace"] += table["flatten"] * units["flatten"]
     dom = max(stages, key=lambda k: stages[k][0])
     t_ms, cnt = stages[dom]
     mean_s = t_ms / cnt / 1e3
@@ -829,6 +833,8 @@ def roofline(wname, lay, prof, ms_step, precision, tiling):
     achieved = flops / mean_s / 1e12
     peak = FP64_VECTOR_PEAK_TFLOPS if precision == 0 else FP32_VECTOR_PEAK_TFLOPS
     rec = recorded_record(dom, wname, tiling) if precision == 0 else None
+    # the whole step's bytes stand in the record of either kernel
+    step_rec = rec or (recorded_record("riemann2", wname, tiling) if precision == 0 else None)
     step_flops = sum(table[k] * units[k] for k in STAGES)
     alg = algorithmic_bytes_per_step(lay)
     name = dom
@@ -849,9 +855,9 @@ def roofline(wname, lay, prof, ms_step, precision, tiling):
          "units_per_launch": units[dom] if name == dom else None,
          "clock_ghz": rec.get("clock_ghz") if rec else None,
          "valu_issue_util": rec.get("valu_util") if rec else None,
-         "step_traffic": rec.get("step_traffic_bytes") if rec else None,
-         "step_traffic_GBps": (rec["step_traffic_bytes"] / (ms_step / 1e3) / 1e9
-                               if rec and rec.get("step_traffic_bytes") else None),
+         "step_traffic": step_rec.get("step_traffic_bytes") if step_rec else None,
+         "step_traffic_GBps": (step_rec["step_traffic_bytes"] / (ms_step / 1e3) / 1e9
+                               if step_rec and step_rec.get("step_traffic_bytes") else None),
          "step_flop_rate_tflops": step_flops / (ms_step / 1e3) / 1e12,
          "hbm": {"algorithmic_bytes_per_step": alg, "achieved_GBps": alg / (ms_step / 1e3) / 1e9,
                  "peak_GBps": HBM_PEAK_GBS, "frac": alg / (ms_step / 1e3) / 1e9 / HBM_PEAK_GBS}}
