@@ -676,10 +676,11 @@ def algorithmic_bytes_per_step(lay):
 
 
 # The final stage's launch forms (ppm_set_step_form): the staged riemann3 +
-# update kernels, the brick kernel, the streamed kernel; the front end's
+# update kernels, the brick kernel, the streamed kernel, one of these or the
+# columns by the level's size, the column kernel; the front end's
 # (ppm_set_front_form): staged trace + riemann1, streamed along z, the x
 # axis fused, every axis fused.
-FINAL_FORMS = ("staged", "brick", "streamed")
+FINAL_FORMS = ("staged", "brick", "streamed", "by_size", "columns")
 FRONT_FORMS = ("staged", "streamed", "x_fused", "xyz_fused")
 
 
@@ -806,9 +807,9 @@ def roofline(wname, lay, prof, ms_step, precision, tiling):
     # riemann3 and update work, timed in the riemann3 slot.  The fused front
     # ends are timed in the trace slot: form 2 (x fused) holds the x axis's
     # riemann1 work there, the riemann1 slot the y and z axes'; forms 1 and 3
-    # hold all of it there.  Form 0 of either picks a fused kernel by the
-    # level's size: the slot it leaves is empty but for its two events
-    fused = (len(tiling) > 2 and tiling[2] != 0) or 0 < prof["update"][0] < 0.05 * prof["riemann3"][0]
+    # hold all of it there.  Final form 3 and front form 2 pick a fused kernel
+    # by the level's size: the slot it leaves is empty but for its two events
+    fused = (len(tiling) > 2 and tiling[2] in (1, 2, 4)) or 0 < prof["update"][0] < 0.05 * prof["riemann3"][0]
     front = tiling[3] if len(tiling) > 3 else 0
     if front == 2 and 0 < prof["riemann1"][0] < 0.05 * prof["trace"][0]:
         front = 3
@@ -839,9 +840,10 @@ def roofline(wname, lay, prof, ms_step, precision, tiling):
     alg = algorithmic_bytes_per_step(lay)
     name = dom
     if fused and dom == "riemann3":
-        name = {0: "riemann3 + update, bricks or columns by rule",
-                1: "final_update (riemann3 + update, brick form)",
-                2: "final_stream (riemann3 + update, streamed form)"}[tiling[2] if len(tiling) > 2 else 0]
+        name = {1: "final_update (riemann3 + update, brick form)",
+                2: "final_stream (riemann3 + update, streamed form)",
+                3: "riemann3 + update, bricks or columns by size",
+                4: "final_columns (riemann3 + update, columns)"}[tiling[2] if len(tiling) > 2 else 3]
     elif front and dom == "trace":
         name = f"trace slot ({FRONT_FORMS[front]} front end: its fused kernels and any staged trace)"
     elif front == 2 and dom == "riemann1":

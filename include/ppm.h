@@ -363,12 +363,8 @@ int ppm_graph_destroy(ppm_graph* g);
 int ppm_set_tiling(ppm_ctx* ctx, int32_t tile, int32_t strip_rows);
 int ppm_get_tiling(const ppm_ctx* ctx, int32_t* tile, int32_t* strip_rows);
 
-/* Form of the step's last stage.  fused = 0 (the default): chosen by the
- * level's size.  On small levels (and in FP32 on large boxes) the final fluxes
- * go to the workspace and a separate kernel updates the zones; on large FP64
- * boxes one kernel whose lanes walk columns of zones along z does both, the
- * final fluxes kept in registers; otherwise the bricks of form 1 do.
- * fused = 1: the final fluxes of each brick of 32 x 4 x 4 valid zones are
+/* Form of the step's last stage.  fused = 0: the final fluxes go to the
+ * workspace and a separate kernel updates the zones.  fused = 1: the final fluxes of each brick of 32 x 4 x 4 valid zones are
  * computed into LDS and the brick is updated from them in the same kernel
  * (the fluxes on a brick's faces are computed by both bricks that share
  * them).  fused = 2: each workgroup owns an x-y tile of valid zones
@@ -376,11 +372,14 @@ int ppm_get_tiling(const ppm_ctx* ctx, int32_t* tile, int32_t* strip_rows);
  * its lanes solve every x and y face of the tile and each zone's high z
  * face once into LDS (the high z faces serve as the next plane's low ones),
  * then update the plane (only the faces shared with neighbouring tiles and
- * runs are solved twice).  In the fused forms nothing is written to the
- * workspace's final-flux planes.  Results are identical bit for bit in all
- * forms.  The species step always runs the staged form (it reads the final
- * mass fluxes from the workspace).  The autotuner picks among the forms and
- * the tile shape. */
+ * runs are solved twice).  fused = 3 (the default): form 0, 1 or 4 by the
+ * precision and the level's size.  fused = 4: one kernel whose lanes walk
+ * columns of zones along z, the final fluxes kept in registers, in FP64; steps
+ * in FP32 run form 0.  In the fused forms no final flux is written to the
+ * workspace.  Results are identical bit for bit in all forms.  The species
+ * step always runs form 0 (it reads the final mass fluxes from the
+ * workspace).  The autotuner picks among forms 0, 1, 2 and 4 and the tile
+ * shape. */
 int ppm_set_step_form(ppm_ctx* ctx, int32_t fused);
 int ppm_get_step_form(const ppm_ctx* ctx, int32_t* fused);
 /* Tile of the streamed final stage (form 2): sx x sy valid zones in x-y
@@ -430,9 +429,9 @@ int ppm_get_front_tiling(const ppm_ctx* ctx, int32_t* sx, int32_t* sy, int32_t* 
  * (ppm_hydro_step_dt, the next dt left on the device; reps steps after one
  * warm-up, HIP events on the stream) from the filled state U into Unew for
  * every candidate tile size x strip height, keeps the fastest, then times
- * the final stage by rule (form 0), in bricks (form 1) and streamed (form 2)
- * with several tile shapes and keeps the fastest, and appends the choice
- * to the JSON-lines
+ * the final stage staged (form 0), in bricks (form 1), streamed (form 2)
+ * with several tile shapes and on large FP64 levels in columns (form 4),
+ * keeps the fastest, and appends the choice to the JSON-lines
  * file cache_path (may be null) keyed by device architecture, precision
  * and the histogram of box extents; a matching entry in the file is
  * applied without timing (*from_cache = 1).  Synchronises.  Writes the

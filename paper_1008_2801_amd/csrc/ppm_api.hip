@@ -372,7 +372,7 @@ namespace {
 void build_bricks(ppm_ctx& c) {
   c.bricks.clear();
   c.tB_begin.assign(1, 0);
-  const int* E = c.fused == 2 ? c.stream_e : BRICK_E;
+  const int* E = c.fused == FINAL_STREAM ? c.stream_e : BRICK_E;
   for (int b = 0; b < c.layout.nbox; ++b) {
     int n[3];
     for (int d = 0; d < 3; ++d) n[d] = c.boxes[b].hi[d] - c.boxes[b].lo[d] + 1;
@@ -880,10 +880,11 @@ int ppm_hydro_step_noalloc(ppm_ctx* ctx, const double* U, double* Unew, double* 
 
 int ppm_set_step_form(ppm_ctx* ctx, int32_t fused) {
   if (!ctx) return PPM_EINVAL;
-  if (fused < 0 || fused > 2) return ctx->fail(PPM_EINVAL, "set_step_form: fused must be 0, 1 or 2");
+  if (fused < FINAL_STAGED || fused > FINAL_COLUMNS)
+    return ctx->fail(PPM_EINVAL, "set_step_form: fused must be 0, 1, 2, 3 or 4");
   if (fused == ctx->fused) return PPM_OK;
   ++ctx->gen;
-  const bool rebuild = (fused == 2) != (ctx->fused == 2);  // forms 0 and 1 share the brick list
+  const bool rebuild = (fused == FINAL_STREAM) != (ctx->fused == FINAL_STREAM);  // the others share the brick list
   ctx->fused = fused;
   if (rebuild) return ctx->hip(upload_bricks(*ctx), "set_step_form");
   return PPM_OK;
@@ -898,7 +899,7 @@ int ppm_set_stream_tiling(ppm_ctx* ctx, int32_t sx, int32_t sy, int32_t sz) {
   ctx->stream_e[0] = sx;
   ctx->stream_e[1] = sy;
   ctx->stream_e[2] = sz;
-  if (ctx->fused == 2) return ctx->hip(upload_bricks(*ctx), "set_stream_tiling");
+  if (ctx->fused == FINAL_STREAM) return ctx->hip(upload_bricks(*ctx), "set_stream_tiling");
   return PPM_OK;
 }
 
@@ -1248,7 +1249,7 @@ int ppm_autotune(ppm_ctx* ctx, const double* U, double* Unew, const double dx[3]
       };
       t = field("tile", 0);
       sr = field("strip_rows", -1);
-      form = field("form", 0);
+      form = field("form", FINAL_STAGED);
       se[0] = field("sx", ctx->stream_e[0]);
       se[1] = field("sy", ctx->stream_e[1]);
       se[2] = field("sz", ctx->stream_e[2]);
@@ -1299,11 +1300,11 @@ int ppm_autotune(ppm_ctx* ctx, const double* U, double* Unew, const double dx[3]
   }
   if (!rc) rc = ppm_set_tiling(ctx, bt, bs);
   // then the final stage's form: the staged pair of kernels, the brick
-  // kernel, or the streamed kernel with one of its tile shapes (x, y
-  // extents, z run)
+  // kernel, the column kernel on a large FP64 level, or the streamed kernel
+  // with one of its tile shapes (x, y extents, z run)
   static const int shapes[][3] = {{16, 8, 32}, {32, 8, 32}, {16, 16, 32}, {32, 4, 32}, {16, 8, 64}, {32, 8, 16},
                                   {64, 4, 32}};
-  int bform = 0, bse[3] = {ctx->stream_e[0], ctx->stream_e[1], ctx->stream_e[2]};
+  int bform = FINAL_STAGED, bse[3] = {ctx->stream_e[0], ctx->stream_e[1], ctx->stream_e[2]};
   const int form0 = ctx->fused;
   auto timed = [&](float& ms) {
     int r = ppm_compute_dt(ctx, U, dx, params, dtv, stream);
@@ -1320,21 +1321,27 @@ int ppm_autotune(ppm_ctx* ctx, const double* U, double* Unew, const double dx[3]
   };
   if (!rc) {
     float ms = 0.f;
-    if (!(rc = ppm_set_step_form(ctx, 0)) && !(rc = timed(ms))) best = ms;
-    if (!rc && !(rc = ppm_set_step_form(ctx, 1)) && !(rc = timed(ms)) && ms < best) {
-      best = ms;
-      bform = 1;
+    if (!(rc = ppm_set_step_form(ctx, FINAL_STAGED)) && !(rc = timed(ms))) best = ms;
+    for (int f : {FINAL_BRICKS, FINAL_COLUMNS}) {
+      if (rc) break;
+      if (f == FINAL_COLUMNS && !final_columns_candidate(ctx->level(), params->precision, (int)ctx->colsF.size()))
+        continue;
+      if ((rc = ppm_set_step_form(ctx, f)) || (rc = timed(ms))) break;
+      if (ms < best) {
+        best = ms;
+        bform = f;
+      }
     }
     for (const auto& sh : shapes) {
       if (rc) break;
       if (ppm_set_stream_tiling(ctx, sh[0], sh[1], sh[2]) != PPM_OK) continue;
-      if ((rc = ppm_set_step_form(ctx, 2)) || (rc = timed(ms))) break;
+      if ((rc = ppm_set_step_form(ctx, FINAL_STREAM)) || (rc = timed(ms))) break;
       if (ms < best) {
         best = ms;
-        bform = 2;
+        bform = FINAL_STREAM;
         for (int d = 0; d < 3; ++d) bse[d] = sh[d];
       }
-      if ((rc = ppm_set_step_form(ctx, 0))) break;
+      if ((rc = ppm_set_step_form(ctx, FINAL_STAGED))) break;
     }
   }
   // then the front end, with the final stage chosen: staged, streamed with

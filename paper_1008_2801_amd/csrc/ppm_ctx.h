@@ -45,7 +45,7 @@ struct ppm_ctx {
   std::vector<int> tY_begin, tZ_begin;  // nbox + 1
   std::vector<Brick> bricks;
   std::vector<int> tB_begin;            // nbox + 1
-  int fused = 0;                        // 1: final fluxes + update in one brick kernel; 2: streamed
+  int fused = FINAL_RULE;               // form of the final stage
   int stream_e[3] = {16, 8, 32};        // tile extents of the streamed final stage
   // front end: 0 trace and stage-1 solves as two staged kernels; 1 one
   // kernel streamed along z over x-y tiles of the traced grids (fbricks,

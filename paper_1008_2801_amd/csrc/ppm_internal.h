@@ -160,6 +160,12 @@ struct InflowView {
   int ext[3];
 };
 
+// Forms of the final stage (ppm_set_step_form): final fluxes and update in two
+// kernels; in one brick kernel (fluxes kept in LDS); the same in x-y tiles
+// streamed along z (k_final_stream); one of these or the columns by the level's
+// size (final_form); in columns along z (FP64; FP32 steps run the two kernels).
+enum { FINAL_STAGED = 0, FINAL_BRICKS = 1, FINAL_STREAM = 2, FINAL_RULE = 3, FINAL_COLUMNS = 4 };
+
 // Launch-side views of the context's device data.
 struct DevLevel {
   const DevBox* boxes;
@@ -181,9 +187,7 @@ struct DevLevel {
   int tile;            // zones per tile of the tile lists (threads per workgroup)
   InflowView inflow;
   const Brick* bricks;  // valid-zone blocks of every box (fused final stage)
-  int fused;            // 0: the final stage's form by rule (step_impl); 1: final fluxes and update in one
-                        // brick kernel (fluxes kept in LDS);
-                        // 2: the same in x-y tiles streamed along z (ppm_kernels.hip, k_final_stream)
+  int fused;            // FINAL_*: the final stage's form
   int stream_e[3];      // form 2: x, y extents of a tile (threads = product) and the z run
   const Brick* fbricks; // traced-grid x-y tiles with z runs (streamed front end)
   int front;            // 1: trace + stage-1 solves in one kernel streamed along z (k_front_stream);
@@ -230,6 +234,10 @@ struct StepStart {
   double h[3], g[3];
   double* dt_next;
 };
+
+// Whether the columns of the final stage are worth timing on a whole level of
+// nCol of them.
+bool final_columns_candidate(const DevLevel& L, int precision, int nCol);
 
 hipError_t launch_step(const DevLevel& L, int precision, int tS0, int tS1, int tE0, int tE1, int tB0, int tB1,
                        int tF0, int tF1, const FrontRanges& fr,

@@ -1067,6 +1067,15 @@ template <class S> bool final_bricks_pay(long long zones, int bricks) {
   return bricks >= 512 && (sizeof(S) == 8 || zones < 512000);
 }
 
+// The form that the final stage of a launch of nB bricks or nCol columns takes.
+template <class S> int final_form(const DevLevel& L, int nB, int nCol) {
+  const long long zones = L.LE / L.nbox;
+  if (L.fused == FINAL_COLUMNS) return sizeof(S) == 8 ? FINAL_COLUMNS : FINAL_STAGED;
+  if (L.fused != FINAL_RULE) return L.fused;
+  if (sizeof(S) == 8 && final_columns_pay(L.LE, zones, nCol)) return FINAL_COLUMNS;
+  return final_bricks_pay<S>(zones, nB) ? FINAL_BRICKS : FINAL_STAGED;
+}
+
 template <class S>
 __global__ void __launch_bounds__(COL_THREADS) __attribute__((amdgpu_waves_per_eu(3)))
 k_final_columns(const Column* __restrict__ cols, int ncols, const DevBox* __restrict__ boxes,
@@ -1585,7 +1594,8 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
   double* fz = flux ? flux[2] : nullptr;
   if (ev) (void)hipEventRecord(ev[5], s);
   const int nB = tB1 - tB0;
-  if (L.fused == 2 && upto == STEP_FULL && nB > 0) {
+  const int last = upto == STEP_FULL ? final_form<S>(L, nB, fr.f1 - fr.f0) : FINAL_STAGED;
+  if (last == FINAL_STREAM) {
     const int sx = L.stream_e[0], sy = L.stream_e[1];
     const size_t lds = sizeof(S) * 5 * (size_t)((sx + 1) * sy + sx * (sy + 1) + 2 * sx * sy);
     hipLaunchKernelGGL(k_final_stream<S>, dim3(xcd_grid(nB)), dim3(stream_threads(sx, sy)), lds, s, L.bricks + tB0,
@@ -1596,11 +1606,7 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
     if (ev) (void)hipEventRecord(ev[7], s);
     return hipGetLastError();
   }
-  const int nCol = fr.f1 - fr.f0;
-  const long long zones = L.LE / L.nbox;
-  const bool columns_last = L.fused == 0 && sizeof(S) == 8 && final_columns_pay(L.LE, zones, nCol);
-  const bool bricks = L.fused == 1 || (L.fused == 0 && !columns_last && final_bricks_pay<S>(zones, nB));
-  if (bricks && upto == STEP_FULL && nB > 0) {
+  if (last == FINAL_BRICKS) {
     hipLaunchKernelGGL(k_final_update<S>, dim3(xcd_grid(nB)), dim3(BRICK_THREADS), 0, s, L.bricks + tB0, nB,
                        L.boxes, (const S*)ework, L.LE, G, L.consts, U, Unew, fx, fy, fz, G.grav, g[0], g[1], g[2],
                        so, L.flags);
@@ -1609,7 +1615,8 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
     return hipGetLastError();
   }
   if constexpr (sizeof(S) == 8) {
-    if (columns_last && upto == STEP_FULL) {
+    if (last == FINAL_COLUMNS) {
+      const int nCol = fr.f1 - fr.f0;
       hipLaunchKernelGGL(k_final_columns<S>, dim3(xcd_grid(nCol)), dim3(COL_THREADS), 0, s, L.colsF + fr.f0, nCol,
                          L.boxes, (const S*)ework, L.LE, G, L.consts, U, Unew, fx, fy, fz, G.grav, g[0], g[1], g[2],
                          so, L.flags);
@@ -1655,6 +1662,10 @@ hipError_t launch_compute_dt(const DevLevel& L, int tile_begin, int tile_end, co
     hipLaunchKernelGGL(k_wavespeed, dim3(n < 2048 ? n : 2048), dim3(L.tile), 0, s, L.tilesE + tile_begin, n, L.boxes, U,
                        h[0], h[1], h[2], gamma, gamma - 1.0, small_pres, dt_dev, cfl);
   return hipGetLastError();
+}
+
+bool final_columns_candidate(const DevLevel& L, int precision, int nCol) {
+  return precision == 0 && columns_pay<double>(L.LE, nCol);
 }
 
 hipError_t launch_step(const DevLevel& L, int precision, int tS0, int tS1, int tE0, int tE1, int tB0, int tB1,

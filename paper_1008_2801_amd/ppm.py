@@ -410,7 +410,8 @@ class Level:
     def set_step_form(self, fused):
         """0/False: the staged final-flux and update kernels; 1/True: one
         brick kernel (fluxes in LDS); 2: the streamed kernel (x-y tiles
-        walked along z).  Same results."""
+        walked along z); 3 (the default): 0, 1 or 4 by the level's size; 4: one
+        kernel in columns along z (FP64).  Same results."""
         self._check(lib().ppm_set_step_form(self.ctx, int(fused)), "ppm_set_step_form")
 
     def get_step_form(self):
