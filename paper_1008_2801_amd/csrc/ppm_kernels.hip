@@ -1104,7 +1104,10 @@ k_final_columns(const Column* __restrict__ cols, int ncols, const DevBox* __rest
   const int N0 = B.n[0] + 2 * NG, N1 = B.n[1] + 2 * NG, N2 = B.n[2] + 2 * NG;
   const long long NS = (long long)N0 * N1 * N2;
   long long ui = B.soff + ((long long)(C.k0 + NG) * N1 + (y + NG)) * N0 + (x + NG);
-  int flz = 0, flx = 0;  // floors met on the zone's y and z faces, on its low x face
+  // floors met on the zone's y and z faces, on its low x face (whose low state's
+  // come with it from the lane below: the first zone's lane has no face, and the
+  // last one's high state is on none)
+  int flz = 0, flx = 0;
   double s = 0.0;
   S zhi[5], fzl[5], zy[5], zx1[5];  // carried from plane to plane
   {
@@ -1130,7 +1133,8 @@ k_final_columns(const Column* __restrict__ cols, int ncols, const DevBox* __rest
       stage3_state<2, 1>(w, LE, G, Dxy, c2x, Dyx, c2y, lo, flz);
       wall_states<2>(B, k, zhi, lo);
       riemann<2>(zhi, lo, G, F, flz);
-      stage3_state<2, 0>(w, LE, G, Dxy, c2x, Dyx, c2y, zhi, flz);
+      // not above the run's last plane, which on the box's last is no face
+      if (k < C.k1) stage3_state<2, 0>(w, LE, G, Dxy, c2x, Dyx, c2y, zhi, flz);
     }
     if (fz && zone && (k > C.k0 || k == 0)) {
       const int xs[3] = {x, y, k};
@@ -1151,10 +1155,12 @@ k_final_columns(const Column* __restrict__ cols, int ncols, const DevBox* __rest
           Dzy[m] = a[m] - zy[m];
           zy[m] = a[m];
         }
-        stage3_state<0, 0>(v, LE, G, Dyz, c2y, Dzy, c2z, hi, flx);
+        int flh = 0;
+        stage3_state<0, 0>(v, LE, G, Dyz, c2y, Dzy, c2z, hi, flh);
         stage3_state<0, 1>(v, LE, G, Dyz, c2y, Dzy, c2z, lo, flx);
 #pragma unroll
         for (int m = 0; m < 5; ++m) hi[m] = __shfl_up(hi[m], 1, 64);
+        flx |= __shfl_up(flh, 1, 64);
         wall_states<0>(B, x, hi, lo);
         riemann<0>(hi, lo, G, H, flx);
         if (fx && face) {
