@@ -120,7 +120,10 @@ int ppm_flux_offsets(const ppm_ctx* ctx, int32_t d, int64_t* off);
 /* Device scratch for the step, owned by the caller: bytes needed for the
  * given precision, then the buffer to use (kept until replaced; must stay
  * allocated while work that uses it is in flight).  The step returns
- * PPM_EINVAL if no large-enough workspace is set. */
+ * PPM_EINVAL if no large-enough workspace is set.  Steps of one context may
+ * be in flight together (on several streams) if each was given a workspace
+ * of its own and their dt, dx and gravity are equal: the context holds one
+ * set of the constants formed from these, and one set of status flags. */
 size_t ppm_workspace_bytes(const ppm_ctx* ctx, int32_t precision);
 int ppm_set_workspace(ppm_ctx* ctx, void* dev_ptr, size_t bytes);
 

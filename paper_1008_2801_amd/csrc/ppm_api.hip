@@ -780,8 +780,8 @@ int ppm_compute_dt(ppm_ctx* ctx, const double* U, const double dx[3], const ppm_
 
 static StepStart step_start(double dt, const double* dt_dev, const double dx[3], const ppm_params* params,
                             double* dt_next) {
-  StepStart st{true, dt, dt_dev, {dx[0], dx[1], dx[2]}, {params->grav[0], params->grav[1], params->grav[2]}, dt_next};
-  return st;
+  return StepStart{true, dt, dt_dev, {dx[0], dx[1], dx[2]}, {params->grav[0], params->grav[1], params->grav[2]},
+                   dt_next, {}};
 }
 
 // work: the step workspace (null: the context's, ppm_set_workspace) and its
@@ -813,8 +813,8 @@ static int hydro_step_impl(ppm_ctx* ctx, const double* U, double* Unew, double* 
   hipStream_t s = (hipStream_t)stream;
   const DevLevel L = ctx->level();
   int rc = PPM_OK;
-  const SpeedOut so{dt_next, L.consts->speed, params->cfl, {dx[0], dx[1], dx[2]}, params->gamma, params->gamma - 1.0,
-                    params->small_pres};
+  const SpeedOut so{dt_next, params->cfl, {dx[0], dx[1], dx[2]}, params->gamma, params->gamma - 1.0,
+                    params->small_pres, {}};
   StepStart st = step_start(dt, dt_dev, dx, params, dt_next);
   const int grav = (params->grav[0] != 0.0 || params->grav[1] != 0.0 || params->grav[2] != 0.0) ? 1 : 0;
   auto run = [&](int tS0, int tS1, int tE0, int tE1, int tB0, int tB1, int tF0, int tF1, const FrontRanges& fr,

@@ -131,15 +131,26 @@ inline __host__ __device__ int inv_axis_class(int y, int n) { return (y < NG ? 1
 
 // Per-step constants formed on the device from dt (so that a graph can take
 // dt from device memory).  The reconstruction copies exist in FP64 and FP32.
-constexpr int SPEED_SLOTS = 16;
 struct StepConsts {
   double dt, hdt;
   double dtdx[3];
   double d_dtdx[3], d_dt2h[3], d_dt3h[3], d_hdtg[3];
   float f_dtdx[3], f_dt2h[3], f_dt3h[3], f_hdtg[3];
-  // largest speed of the update's workgroups by index modulo the slots, a cache
-  // line each (the bits of non-negative doubles)
-  alignas(128) unsigned long long speed[SPEED_SLOTS][16];
+};
+
+// The largest speed of the update's workgroups by index modulo the slots (the
+// bits of non-negative doubles).  They belong to a step, not to its context,
+// so that steps in flight on two streams do not meet in them: each lies at the
+// start of one of the workspace's final-flux planes, in the first box's layer
+// z = -1 (nine zones at least), which holds no face of a valid zone and so is
+// read and written by no stage.  first: the first such plane, plane: its bytes.
+constexpr int SPEED_SLOTS = 15;
+struct SpeedSlots {
+  char* first;
+  long long plane;
+  __host__ __device__ unsigned long long* at(int k) const {
+    return (unsigned long long*)(((size_t)(first + k * plane) + 7) & ~(size_t)7);
+  }
 };
 
 // Number of planes in the traced-grid (E) arena: flattening 1, traces 30,
@@ -218,21 +229,22 @@ enum { STEP_TO_STAGE2 = 5, STEP_FULL = 7, STEP_FULL_STAGED = 8 };
 // dt[0] = cfl / dt[1].
 struct SpeedOut {
   double* dt;
-  unsigned long long (*slots)[16];  // StepConsts::speed
   double cfl;
   double h[3];
   double gamma, gm1, small_pres;
+  SpeedSlots slots;  // set at launch
 };
 
 // What the first launch of a step does besides its conversion: the step's
 // constants (L.consts) from dt (dt_dev[0] if given), the spacings and gravity,
-// and the next dt's pair cleared (dt_next, when not null).
+// and the next dt's pair and the speed slots cleared (dt_next, when not null).
 struct StepStart {
   bool on;
   double dt;
   const double* dt_dev;
   double h[3], g[3];
   double* dt_next;
+  SpeedSlots slots;  // set at launch
 };
 
 // Whether the columns of the final stage are worth timing on a whole level of

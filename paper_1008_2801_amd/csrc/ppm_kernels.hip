@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(MAX_TILE) k_prim(const Tile* __restrict__ tile
       step_consts(consts, st.dt, st.dt_dev, st.h[0], st.h[1], st.h[2], st.g[0], st.g[1], st.g[2]);
       if (st.dt_next) clear_speed(st.dt_next);  // after dt was read, which may be the same
     }
-    if (threadIdx.x < SPEED_SLOTS) consts->speed[threadIdx.x][0] = 0ull;
+    if (st.dt_next && threadIdx.x < SPEED_SLOTS) *st.slots.at(threadIdx.x) = 0ull;
     return;
   }
   prim_body(xcd_tile(ntiles), tiles, boxes, U, prim, LS, G, flags);
@@ -906,11 +906,11 @@ __device__ __forceinline__ double fold_signal_speed(double s, double r, double m
 // already as large, and a minimum only from those that raised it (one from each
 // costs a 256 x 256 x 4 step 7 us).  On a level that the chip holds at once all
 // workgroups come here together, before any has raised the maximum, and queue
-// at its address: slots (the workgroups by index, and so by XCD) each let only
+// at its address: slots (the workgroups by index) each let only
 // the workgroups pass that raise the slot's own maximum (256 x 256 x 4: k_update
 // 25.1 -> 14.5 us, 64^3: 19.6 -> 12.8).  Every lane of the workgroup must call it.
 __device__ __forceinline__ void block_speed_to(double s, double* dt, double cfl,
-                                               unsigned long long (*slots)[16] = nullptr) {
+                                               SpeedSlots slots = {}) {
   for (int off = 32; off > 0; off >>= 1) s = smax(s, __shfl_xor(s, off, 64));
   __shared__ double wmax[MAX_TILE / 64];
   if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = s;
@@ -920,8 +920,8 @@ __device__ __forceinline__ void block_speed_to(double s, double* dt, double cfl,
     for (int w = 1; w < (int)(blockDim.x / 64); ++w) m = smax(m, wmax[w]);
     const unsigned long long mb = (unsigned long long)__double_as_longlong(m);
     unsigned long long* bits = (unsigned long long*)dt;
-    if (slots) {
-      unsigned long long* slot = slots[blockIdx.x % SPEED_SLOTS];
+    if (slots.first) {
+      unsigned long long* slot = slots.at(blockIdx.x % SPEED_SLOTS);
       if (mb <= __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || mb <= atomicMax(slot, mb)) return;
     }
     if (mb > __hip_atomic_load(bits + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) && mb > atomicMax(bits + 1, mb))
@@ -1538,9 +1538,10 @@ template <class S>
 hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int tB0, int tB1, int tF0, int tF1,
                      const FrontRanges& fr, const double* U,
                      double* Unew, double* const* flux, void* work, Gas<S> G, const double g[3], hipStream_t s,
-                     hipEvent_t* ev, int upto, const SpeedOut& so, const StepStart& st) {
+                     hipEvent_t* ev, int upto, SpeedOut so, StepStart st) {
   S* prim = (S*)work;
   S* ework = prim + P_PLANES * L.LS;
+  so.slots = st.slots = SpeedSlots{(char*)(ework + E_F3 * L.LE), (long long)sizeof(S) * L.LE};
   const int nS = tS1 - tS0, nE = tE1 - tE0;
   const Tile* TS = L.tilesS + tS0;
   const Tile* TE = L.tilesE + tE0;
