@@ -83,9 +83,15 @@ def traffic_record_path(kernel, workload):
     return os.path.join(ROOT, "profiles", f"traffic_{kernel}_{workload}.json")
 
 
+# The kernels of a stage's slot, where they are not one kernel of the stage's
+# name: the fused front ends and final stages, whichever of them run.
+SLOT_KERNELS = {"trace": ("trace", "front_x", "front_yz", "front_small", "front_stream"),
+                "riemann3": ("riemann3", "final_update", "final_columns", "final_stream")}
+
+
 def record_traffic(fetch_csv, write_csv, kernel, workload, tiling, fetch_factor, write_factor, valu_csv=None):
-    """Mean FETCH_SIZE / WRITE_SIZE (KiB per dispatch) of the kernel from two
-    rocprofv3 --pmc runs, times the factors a plain copy of known size gives,
+    """FETCH_SIZE / WRITE_SIZE (KiB per step) of the kernel, or of the kernels
+    of its slot (SLOT_KERNELS), from two rocprofv3 --pmc runs, times the factors a plain copy of known size gives,
     stored with the digest of the kernel sources and the tiling.  With
     valu_csv (a third run with SQ_INSTS_VALU and GRBM_GUI_ACTIVE): the
     kernel's VALU issue utilisation, SQ_INSTS_VALU x 4 cycles (a wave64 FP64
@@ -93,20 +99,24 @@ def record_traffic(fetch_csv, write_csv, kernel, workload, tiling, fetch_factor,
     kernel's cycles (GRBM_GUI_ACTIVE / 8 XCDs), and the sustained clock,
     those cycles over the dispatch's duration."""
     import csv
+    names = [f"k_{k}<double>" for k in SLOT_KERNELS.get(kernel, (kernel,))]
 
-    def mean_kib(path, counter):
-        vals = [float(r["Counter_Value"]) for r in csv.DictReader(open(path))
-                if r["Counter_Name"] == counter and f"k_{kernel}<double>" in r["Kernel_Name"]]
-        if not vals:
-            raise SystemExit(f"no {counter} records of k_{kernel}<double> in {path}")
-        return sum(vals) / len(vals), len(vals)
-    f_kib, nf = mean_kib(fetch_csv, "FETCH_SIZE")
-    w_kib, nw = mean_kib(write_csv, "WRITE_SIZE")
+    def of_slot(r):
+        return any(n in r["Kernel_Name"] for n in names)
+
+    def step_kib(path, counter):
+        rows = [r for r in csv.DictReader(open(path)) if r["Counter_Name"] == counter]
+        vals = [float(r["Counter_Value"]) for r in rows if of_slot(r)]
+        steps = sum("k_riemann2<double>" in r["Kernel_Name"] for r in rows)
+        if not vals or not steps:
+            raise SystemExit(f"no {counter} records of {names} in {path}")
+        return sum(vals) / steps, steps
+    f_kib, nf = step_kib(fetch_csv, "FETCH_SIZE")
+    w_kib, nw = step_kib(write_csv, "WRITE_SIZE")
 
     def step_bytes(path, counter, factor):
         # every kernel of the steps, per step: the counted dispatches over
-        # the step count, which the kernel's own dispatches give.  A
-        # stand-alone dt pass (k_clear_speed, k_wavespeed) is not part of a
+        # the step count.  A stand-alone dt pass (k_clear_speed, k_wavespeed) is not part of a
         # step.
         rows = sorted((r for r in csv.DictReader(open(path))
                        if r["Counter_Name"] == counter and "ppm::" in r["Kernel_Name"]),
@@ -117,9 +127,10 @@ def record_traffic(fetch_csv, write_csv, kernel, workload, tiling, fetch_factor,
                 continue
             tot += float(r["Counter_Value"])
         return tot * 1024 * factor
-    steps = nf  # one dispatch of the kernel per step
-    rec = {"kernel": f"k_{kernel}<double>", "workload": workload, "tiling": list(tiling),
-           "fetch_kib_per_dispatch": f_kib, "write_kib_per_dispatch": w_kib, "dispatches": [nf, nw],
+    steps = nf
+    rec = {"kernel": " + ".join(sorted({n for r in csv.DictReader(open(fetch_csv)) for n in names
+                                        if n in r["Kernel_Name"]})), "workload": workload, "tiling": list(tiling),
+           "fetch_kib_per_step": f_kib, "write_kib_per_step": w_kib, "steps": [nf, nw],
            "fetch_factor": fetch_factor, "write_factor": write_factor,
            "read_bytes_per_launch": f_kib * 1024 * fetch_factor,
            "write_bytes_per_launch": w_kib * 1024 * write_factor,
@@ -128,22 +139,24 @@ def record_traffic(fetch_csv, write_csv, kernel, workload, tiling, fetch_factor,
     rec["step_traffic_bytes"] = (step_bytes(fetch_csv, "FETCH_SIZE", fetch_factor) +
                                  step_bytes(write_csv, "WRITE_SIZE", write_factor)) / steps
     if valu_csv:
-        rows = [r for r in csv.DictReader(open(valu_csv)) if f"k_{kernel}<double>" in r["Kernel_Name"]]
+        rows = [r for r in csv.DictReader(open(valu_csv)) if of_slot(r)]
         by = {}
         for r in rows:
             by.setdefault(r["Dispatch_Id"], {})[r["Counter_Name"]] = (float(r["Counter_Value"]), r)
-        utils, clocks = [], []
+        insts = cycles = 0.0
+        clocks = []
         for d in by.values():
             if "SQ_INSTS_VALU" in d and "GRBM_GUI_ACTIVE" in d:
                 cyc = d["GRBM_GUI_ACTIVE"][0] / 8.0
-                utils.append(d["SQ_INSTS_VALU"][0] * 4.0 / (1024.0 * cyc))
+                insts += d["SQ_INSTS_VALU"][0]
+                cycles += cyc
                 r0 = d["GRBM_GUI_ACTIVE"][1]
                 if r0.get("Start_Timestamp") and r0.get("End_Timestamp"):
                     ns = float(r0["End_Timestamp"]) - float(r0["Start_Timestamp"])
                     if ns > 0:
                         clocks.append(cyc / ns)
-        if utils:
-            rec["valu_util"] = sum(utils) / len(utils)
+        if cycles:
+            rec["valu_util"] = insts * 4.0 / (1024.0 * cycles)
         if clocks:
             rec["clock_ghz"] = sum(clocks) / len(clocks)
     with open(traffic_record_path(kernel, workload), "w") as fh:
@@ -681,7 +694,9 @@ def algorithmic_bytes_per_step(lay):
 # (ppm_set_front_form): staged trace + riemann1, streamed along z, the x
 # axis fused, every axis fused.
 FINAL_FORMS = ("staged", "brick", "streamed", "by_size", "columns")
-FRONT_FORMS = ("staged", "streamed", "x_fused", "xyz_fused")
+FRONT_FORMS = ("staged", "streamed", "x_fused_yz_by_size", "xyz_fused")
+# What a step's front end runs (ppm_get_step_route).
+FRONT_KERNELS = ("staged", "streamed", "x_fused", "x_fused_yz_columns", "one_launch")
 
 
 def launch_config(lev):
@@ -731,9 +746,11 @@ def headline(wl, wname, steps, warmup, per_box=True, tiling=None, autotune=True)
         t_, s_, from_cache = lev.autotune(Uf, wl.dx, p, reps=2, cache_path=AUTOTUNE_CACHE)
         del Uf
     tiling = launch_config(lev)
+    route = lev.get_step_route(p.precision)
     zones = lay.valid_zones()
     out = {"tiling": {"tile": tiling[0], "strip_rows": tiling[1], "final_stage_form": FINAL_FORMS[tiling[2]],
-                      "front_end_form": FRONT_FORMS[tiling[3]], "extents": tiling[4:] or None},
+                      "front_end_form": FRONT_FORMS[tiling[3]], "extents": tiling[4:] or None,
+                      "final_stage_kernels": FINAL_FORMS[route[1]], "front_end_kernels": FRONT_KERNELS[route[0]]},
            "autotune": {"from_cache": None if from_cache is None else bool(from_cache),
                         "cache": os.path.relpath(AUTOTUNE_CACHE, ROOT) if from_cache is not None else None}}
 
@@ -790,10 +807,10 @@ def headline(wl, wname, steps, warmup, per_box=True, tiling=None, autotune=True)
     lev._work = None
     del U0, lev
     torch.cuda.empty_cache()
-    return out, prof, tiling
+    return out, prof, tiling, route
 
 
-def roofline(wname, lay, prof, ms_step, precision, tiling):
+def roofline(wname, lay, prof, ms_step, precision, tiling, route):
     """The dominant stage kernel's algorithmic flop rate against the vector
     peak of its precision, with the recorded counter figures of the same
     kernel and workload (null once the kernel sources or the tiling
@@ -803,29 +820,25 @@ def roofline(wname, lay, prof, ms_step, precision, tiling):
         for k, v in stage_units(lay.n(b)).items():
             units[k] += v
     table = flops_table(wname)
-    # with a fused final stage (brick or streamed form) one kernel does the
-    # riemann3 and update work, timed in the riemann3 slot.  The fused front
-    # ends are timed in the trace slot: form 2 (x fused) holds the x axis's
-    # riemann1 work there, the riemann1 slot the y and z axes'; forms 1 and 3
-    # hold all of it there.  Final form 3 and front form 2 pick a fused kernel
-    # by the level's size: the slot it leaves is empty but for its two events
-    fused = (len(tiling) > 2 and tiling[2] in (1, 2, 4)) or 0 < prof["update"][0] < 0.05 * prof["riemann3"][0]
-    front = tiling[3] if len(tiling) > 3 else 0
-    if front == 2 and 0 < prof["riemann1"][0] < 0.05 * prof["trace"][0]:
-        front = 3
-    stages = {k: prof[k] for k in STAGES if not (fused and k == "update") and not (front in (1, 3) and k == "riemann1")}
+    # a fused final stage does the riemann3 and update work in one kernel,
+    # timed in the riemann3 slot.  The fused front ends are timed in the trace
+    # slot: with x fused it holds the x axis's riemann1 work, the riemann1 slot
+    # the y and z axes'; the other fused ones hold all of it there.  Where
+    # k_front_x runs, it forms the flattening coefficients too.
+    front, final = route
+    fused = final != 0
+    stages = {k: prof[k] for k in STAGES if not (fused and k == "update") and
+              not (front in (1, 3, 4) and k == "riemann1") and not (front in (2, 3) and k == "flatten")}
     flops_of = {k: table[k] * units[k] for k in stages}
     if fused:
         flops_of["riemann3"] += table["update"] * units["update"]
-    if front in (1, 3):
+    if front in (1, 3, 4):
         flops_of["trace"] += table["riemann1"] * units["riemann1"]
     elif front == 2:
         ux = sum(stage_units_axis(lay.n(b), 0) for b in range(lay.nbox))
         flops_of["trace"] += table["riemann1"] * ux
         flops_of["riemann1"] -= table["riemann1"] * ux
-    if front >= 2 and 0 < prof["flatten"][0] < 0.01 * prof["trace"][0]:
-        # the x front end forms the flattening coefficients
-        stages.pop("flatten")
+    if front in (2, 3):
         flops_of["trace"] += table["flatten"] * units["flatten"]
     dom = max(stages, key=lambda k: stages[k][0])
     t_ms, cnt = stages[dom]
@@ -842,10 +855,9 @@ def roofline(wname, lay, prof, ms_step, precision, tiling):
     if fused and dom == "riemann3":
         name = {1: "final_update (riemann3 + update, brick form)",
                 2: "final_stream (riemann3 + update, streamed form)",
-                3: "riemann3 + update, bricks or columns by size",
-                4: "final_columns (riemann3 + update, columns)"}[tiling[2] if len(tiling) > 2 else 3]
+                4: "final_columns (riemann3 + update, columns)"}[final]
     elif front and dom == "trace":
-        name = f"trace slot ({FRONT_FORMS[front]} front end: its fused kernels and any staged trace)"
+        name = f"trace slot ({FRONT_KERNELS[front]} front end: its fused kernels and any staged trace)"
     elif front == 2 and dom == "riemann1":
         name = "riemann1 (y and z axes)"
     r = {"bound": "alu", "kernel": name, "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
@@ -880,8 +892,8 @@ def main():
                     help="autotuner cache file (default: the package's autotune_cache.jsonl)")
     ap.add_argument("--tiling", default=None,
                     help="'tile,strip_rows[,final[,front[,x,y,z[,x,y,z]]]]': use this launch configuration "
-                         "(tiling; final-stage form 0 staged / 1 brick / 2 streamed; front-end form 0 staged / "
-                         "1 streamed / 2 x fused / 3 all fused; the streamed forms' tile extents) instead of "
+                         "(tiling; final-stage form 0 staged / 1 brick / 2 streamed / 3 by size / 4 columns; "
+                         "front-end form 0 staged / 1 streamed / 2 by size / 3 all fused; the streamed forms' tile extents) instead of "
                          "autotuning")
     ap.add_argument("--no-extras", action="store_true",
                     help="skip the other workloads (single box, 512-box tiling, adjoint, two-level, jet, species)")
@@ -944,12 +956,12 @@ def main():
     print(f"bench: workload {args.workload}: {lay.nbox} box(es), {lay.valid_zones()} valid zones", file=sys.stderr,
           flush=True)
     tiling = tuple(int(v) for v in args.tiling.split(",")) if args.tiling else None
-    h, prof, tiling = headline(wl, args.workload, args.steps, args.warmup, per_box=not args.no_per_box,
+    h, prof, tiling, route = headline(wl, args.workload, args.steps, args.warmup, per_box=not args.no_per_box,
                                tiling=tiling, autotune=not args.no_autotune)
     zones = lay.valid_zones()
     print(f"bench: {args.workload} graph {h['graph']:.4g} zone-updates/s ({h['ms_per_step']:.3f} ms/step)",
           file=sys.stderr, flush=True)
-    rf = roofline(args.workload, lay, prof, h["ms_per_step"], wl.precision, tiling)
+    rf = roofline(args.workload, lay, prof, h["ms_per_step"], wl.precision, tiling, route)
     out = {
         "metric": METRIC, "value": h["graph"], "unit": "zone-updates/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": h["ms_per_step"], "higher_is_better": True,
@@ -970,8 +982,8 @@ def main():
         from paper_1008_2801_amd import inputs as I
         print("bench: 256^3 single box (FP64)", file=sys.stderr, flush=True)
         w2 = I.cfg2()
-        r2, p2, t2 = headline(w2, "cfg2", 20, 2, per_box=False)
-        r2["roofline"] = roofline("cfg2", w2.layout, p2, r2["ms_per_step"], 0, t2)
+        r2, p2, t2, k2 = headline(w2, "cfg2", 20, 2, per_box=False)
+        r2["roofline"] = roofline("cfg2", w2.layout, p2, r2["ms_per_step"], 0, t2, k2)
         r2["workload"] = "cfg2: " + WORKLOADS["cfg2"]
         out["single_box_256"] = r2
         del w2
@@ -987,7 +999,7 @@ def main():
         out["multibox"] = extra
         print("bench: the same 512^3 level, FP32 reconstruction", file=sys.stderr, flush=True)
         w5 = I.cfg5(precision=1)
-        r5, p5, t5 = headline(w5, "cfg5-fp32", args.steps, args.warmup, per_box=False)
+        r5, *_ = headline(w5, "cfg5-fp32", args.steps, args.warmup, per_box=False)
         r5["workload"] = "cfg5-fp32: " + WORKLOADS["cfg5-fp32"]
         out["fp32_reconstruction"] = r5
         print("bench: adjoint step of the 512^3 level (FP32 reconstruction)", file=sys.stderr, flush=True)

@@ -428,6 +428,14 @@ int ppm_get_front_form(const ppm_ctx* ctx, int32_t* form);
 int ppm_set_front_tiling(ppm_ctx* ctx, int32_t sx, int32_t sy, int32_t sz);
 int ppm_get_front_tiling(const ppm_ctx* ctx, int32_t* sx, int32_t* sy, int32_t* sz);
 
+/* The kernels that a batched step of the given precision takes in the current
+ * forms and tilings.  *front: 0 trace and normal solves staged, 1 streamed
+ * along z, 2 the x axis in one kernel, y and z staged, 3 the x axis in one
+ * kernel, y and z in columns, 4 all axes in one launch.  *final_stage: 0, 1, 2
+ * or 4 as in ppm_set_step_form.  PPM_EINVAL for a null pointer or another
+ * precision than 0 or 1. */
+int ppm_get_step_route(const ppm_ctx* ctx, int32_t precision, int32_t* front, int32_t* final_stage);
+
 /* Autotuner: times the batched step as graphs and steady loops run it
  * (ppm_hydro_step_dt, the next dt left on the device; reps steps after one
  * warm-up, HIP events on the stream) from the filled state U into Unew for

@@ -945,6 +945,15 @@ int ppm_get_stream_tiling(const ppm_ctx* ctx, int32_t* sx, int32_t* sy, int32_t*
   return PPM_OK;
 }
 
+int ppm_get_step_route(const ppm_ctx* ctx, int32_t precision, int32_t* front, int32_t* final_stage) {
+  if (!ctx || precision < 0 || precision > 1 || !front || !final_stage) return PPM_EINVAL;
+  int f = 0, l = 0;
+  step_route(ctx->level(), precision, (int)ctx->tilesE.size(), (int)ctx->bricks.size(), front_all(*ctx), &f, &l);
+  *front = f;
+  *final_stage = l;
+  return PPM_OK;
+}
+
 int ppm_get_step_form(const ppm_ctx* ctx, int32_t* fused) {
   if (!ctx || !fused) return PPM_EINVAL;
   *fused = ctx->fused;

@@ -177,6 +177,12 @@ struct InflowView {
 // size (final_form); in columns along z (FP64; FP32 steps run the two kernels).
 enum { FINAL_STAGED = 0, FINAL_BRICKS = 1, FINAL_STREAM = 2, FINAL_RULE = 3, FINAL_COLUMNS = 4 };
 
+// Kernels of the front end (the values of ppm_set_front_form, and what form 2
+// takes by size): trace and stage-1 solves as two staged kernels; one kernel
+// streamed along z; x in one kernel (k_front_x), y and z staged; x the same,
+// y and z in columns (k_front_yz); all axes in one launch (k_front_small).
+enum { FRONT_STAGED = 0, FRONT_STREAM = 1, FRONT_X = 2, FRONT_COLUMNS = 3, FRONT_SMALL = 4 };
+
 // Launch-side views of the context's device data.
 struct DevLevel {
   const DevBox* boxes;
@@ -246,6 +252,10 @@ struct StepStart {
   double* dt_next;
   SpeedSlots slots;  // set at launch
 };
+
+// The kernels that a step over these ranges takes (nE tiles of the traced grids,
+// nB bricks): FRONT_* and FINAL_*.
+void step_route(const DevLevel& L, int precision, int nE, int nB, const FrontRanges& fr, int* front, int* last);
 
 // Whether the columns of the final stage are worth timing on a whole level of
 // nCol of them.

@@ -1534,6 +1534,15 @@ template <class S> bool planes_resident(long long LE) {
 // 413, and 8 boxes of 64^3 (120 MB) 392 -> 396.
 template <class S> bool prim_resident(long long LS) { return 5 * LS * (long long)sizeof(S) <= (64ll << 20); }
 
+// The kernels that the front end of a launch takes.
+template <class S> int front_form(const DevLevel& L, int nE, const FrontRanges& fr) {
+  const int nX = fr.x1 - fr.x0, nYZ = fr.y1 - fr.y0 + fr.z1 - fr.z0;
+  if (L.front == 1) return FRONT_STREAM;
+  if (L.front == 0) return FRONT_STAGED;
+  if (L.front == 3 || columns_pay<S>(L.LE, nYZ)) return FRONT_COLUMNS;
+  return L.tile == XF_THREADS && front_small_pays(nX + 2 * nE) ? FRONT_SMALL : FRONT_X;
+}
+
 template <class S>
 hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int tB0, int tB1, int tF0, int tF1,
                      const FrontRanges& fr, const double* U,
@@ -1555,13 +1564,12 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
   if (ev) (void)hipEventRecord(ev[1], s);
   const int nX = fr.x1 - fr.x0, nY = fr.y1 - fr.y0, nZ = fr.z1 - fr.z0;
   const int nF = tF1 - tF0;
-  const int d0 = (L.front >= 2 && nX > 0) ? 1 : 0;
-  const bool columns = d0 && nY + nZ > 0 && (L.front == 3 || columns_pay<S>(L.LE, nY + nZ));
-  const bool small = d0 && !columns && L.tile == XF_THREADS && front_small_pays(nX + 2 * nE);
-  if (!d0 || small)  // else k_front_x does it
+  const int front = front_form<S>(L, nE, fr);
+  const int d0 = front == FRONT_X || front == FRONT_COLUMNS ? 1 : 0;  // k_front_x runs the x axis
+  if (!d0)  // else k_front_x does it
     hipLaunchKernelGGL(k_flatten<S>, dim3(xcd_grid(nE)), blk, 0, s, TE, nE, L.boxes, prim, L.LS, ework, L.LE, G);
   if (ev) (void)hipEventRecord(ev[2], s);
-  if (L.front == 1 && nF > 0) {
+  if (front == FRONT_STREAM) {
     // trace and stage-1 solves in one kernel (timed in the trace slot)
     const int mx = L.front_m[0], my = L.front_m[1];
     const size_t lds = sizeof(S) * 5 * (size_t)((mx + 1) * my + mx * (my + 1));
@@ -1571,16 +1579,15 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
     if (ev) (void)hipEventRecord(ev[3], s);
     if (ev) (void)hipEventRecord(ev[4], s);
   } else {
-    // front forms 2 and 3: the x axis's trace and solves in one kernel, y's and
-    // z's in columns always (3) or where that pays (2) (timed in the trace slot)
-    if (d0 && !small)
+    // fused axes are timed in the trace slot
+    if (d0)
       hipLaunchKernelGGL(k_front_x<S>, dim3(xcd_grid(nX)), dim3(XF_THREADS), 0, s, L.tilesX + fr.x0, nX, L.boxes,
                          (const S*)prim, L.LS, ework, L.LE, G, L.consts, L.flags);
-    if (small) {
+    if (front == FRONT_SMALL) {
       hipLaunchKernelGGL(k_front_small<S>, dim3(xcd_grid(nX + 2 * nE)), dim3(XF_THREADS), 0, s, L.tilesX + fr.x0, nX,
                          TE, nE, L.boxes, (const S*)prim, L.LS, ework, L.LE, G, L.consts, L.flags);
       if (ev) (void)hipEventRecord(ev[3], s);
-    } else if (columns) {
+    } else if (front == FRONT_COLUMNS) {
       hipLaunchKernelGGL(k_front_yz<S>, dim3(xcd_grid(nY + nZ)), dim3(COL_THREADS), 0, s, L.colsY + fr.y0, nY,
                          L.colsZ + fr.z0, nZ, L.boxes, (const S*)prim, L.LS, ework, L.LE, G, L.consts, L.flags);
       if (ev) (void)hipEventRecord(ev[3], s);
@@ -1669,6 +1676,12 @@ hipError_t launch_compute_dt(const DevLevel& L, int tile_begin, int tile_end, co
     hipLaunchKernelGGL(k_wavespeed, dim3(n < 2048 ? n : 2048), dim3(L.tile), 0, s, L.tilesE + tile_begin, n, L.boxes, U,
                        h[0], h[1], h[2], gamma, gamma - 1.0, small_pres, dt_dev, cfl);
   return hipGetLastError();
+}
+
+void step_route(const DevLevel& L, int precision, int nE, int nB, const FrontRanges& fr, int* front, int* last) {
+  const int nCol = fr.f1 - fr.f0;
+  *front = precision == 1 ? front_form<float>(L, nE, fr) : front_form<double>(L, nE, fr);
+  *last = precision == 1 ? final_form<float>(L, nB, nCol) : final_form<double>(L, nB, nCol);
 }
 
 bool final_columns_candidate(const DevLevel& L, int precision, int nCol) {

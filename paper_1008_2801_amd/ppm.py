@@ -31,7 +31,7 @@ SYMBOLS = ("ppm_ctx_create", "ppm_ctx_destroy", "ppm_last_error", "ppm_layout_of
            "ppm_species_workspace_bytes", "ppm_set_species_workspace", "ppm_fill_species",
            "ppm_hydro_step_species", "ppm_amr_create", "ppm_amr_destroy", "ppm_amr_last_error",
            "ppm_amr_sizes", "ppm_amr_fill_fine", "ppm_amr_step", "ppm_set_inflow",
-           "ppm_hydro_step_adjoint_saved", "ppm_set_step_form", "ppm_get_step_form",
+           "ppm_hydro_step_adjoint_saved", "ppm_set_step_form", "ppm_get_step_form", "ppm_get_step_route",
            "ppm_hydro_step_dt", "ppm_hydro_step_noalloc",
            "ppm_set_stream_tiling", "ppm_get_stream_tiling", "ppm_set_front_form", "ppm_get_front_form",
            "ppm_set_front_tiling", "ppm_get_front_tiling")
@@ -130,6 +130,7 @@ def lib():
         L.ppm_set_inflow.argtypes = [_vp, ctypes.c_int32, _vp]
         L.ppm_set_step_form.argtypes = [_vp, ctypes.c_int32]
         L.ppm_get_step_form.argtypes = [_vp, _i32p]
+        L.ppm_get_step_route.argtypes = [_vp, ctypes.c_int32, _i32p, _i32p]
         L.ppm_set_stream_tiling.argtypes = [_vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
         L.ppm_get_stream_tiling.argtypes = [_vp, _i32p, _i32p, _i32p]
         L.ppm_set_front_form.argtypes = [_vp, ctypes.c_int32]
@@ -418,6 +419,14 @@ class Level:
         f = ctypes.c_int32()
         self._check(lib().ppm_get_step_form(self.ctx, ctypes.byref(f)), "ppm_get_step_form")
         return f.value
+
+    def get_step_route(self, precision=0):
+        """(front, final stage): the kernels a batched step takes
+        (ppm_get_step_route)."""
+        f, s = ctypes.c_int32(), ctypes.c_int32()
+        self._check(lib().ppm_get_step_route(self.ctx, int(precision), ctypes.byref(f), ctypes.byref(s)),
+                    "ppm_get_step_route")
+        return f.value, s.value
 
     def set_stream_tiling(self, sx, sy, sz):
         self._check(lib().ppm_set_stream_tiling(self.ctx, int(sx), int(sy), int(sz)), "ppm_set_stream_tiling")
