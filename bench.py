@@ -810,7 +810,7 @@ def headline(wl, wname, steps, warmup, per_box=True, tiling=None, autotune=True)
     return out, prof, tiling, route
 
 
-def roofline(wname, lay, prof, ms_step, precision, tiling, route):
+def roofline(wname, lay, prof, ms_step, precision, tiling, route=None):
     """The dominant stage kernel's algorithmic flop rate against the vector
     peak of its precision, with the recorded counter figures of the same
     kernel and workload (null once the kernel sources or the tiling
@@ -823,12 +823,14 @@ def roofline(wname, lay, prof, ms_step, precision, tiling, route):
     # a fused final stage does the riemann3 and update work in one kernel,
     # timed in the riemann3 slot.  The fused front ends are timed in the trace
     # slot: with x fused it holds the x axis's riemann1 work, the riemann1 slot
-    # the y and z axes'; the other fused ones hold all of it there.  Where
-    # k_front_x runs, it forms the flattening coefficients too.
-    front, final = route
+    # the y and z axes'; the other fused ones hold all of it there.  Where the
+    # library's route (route; the forms of the tiling stand for it otherwise)
+    # has k_front_x, that kernel forms the flattening coefficients too.
+    front, final = route or (tiling[3] if len(tiling) > 3 else 0, tiling[2] if len(tiling) > 2 else 0)
     fused = final != 0
+    flat_x = route is not None and front in (2, 3)
     stages = {k: prof[k] for k in STAGES if not (fused and k == "update") and
-              not (front in (1, 3, 4) and k == "riemann1") and not (front in (2, 3) and k == "flatten")}
+              not (front in (1, 3, 4) and k == "riemann1") and not (flat_x and k == "flatten")}
     flops_of = {k: table[k] * units[k] for k in stages}
     if fused:
         flops_of["riemann3"] += table["update"] * units["update"]
@@ -838,7 +840,7 @@ def roofline(wname, lay, prof, ms_step, precision, tiling, route):
         ux = sum(stage_units_axis(lay.n(b), 0) for b in range(lay.nbox))
         flops_of["trace"] += table["riemann1"] * ux
         flops_of["riemann1"] -= table["riemann1"] * ux
-    if front in (2, 3):
+    if flat_x:
         flops_of["trace"] += table["flatten"] * units["flatten"]
     dom = max(stages, key=lambda k: stages[k][0])
     t_ms, cnt = stages[dom]
