@@ -373,9 +373,15 @@ void build_bricks(ppm_ctx& c) {
   c.bricks.clear();
   c.tB_begin.assign(1, 0);
   const int* E = c.fused == FINAL_STREAM ? c.stream_e : BRICK_E;
+  double zones = 0.0, slots = 0.0, count = 0.0;
   for (int b = 0; b < c.layout.nbox; ++b) {
     int n[3];
     for (int d = 0; d < 3; ++d) n[d] = c.boxes[b].hi[d] - c.boxes[b].lo[d] + 1;
+    double k[3];
+    for (int d = 0; d < 3; ++d) k[d] = (n[d] + BRICK_E[d] - 1) / BRICK_E[d];
+    zones += (double)n[0] * n[1] * n[2];
+    slots += k[0] * std::min(n[0], BRICK_E[0]) * n[1] * n[2];
+    count += k[0] * k[1] * k[2];
     for (int z = 0; z < n[2]; z += E[2])
       for (int y = 0; y < n[1]; y += E[1])
         for (int x = 0; x < n[0]; x += E[0]) {
@@ -391,6 +397,8 @@ void build_bricks(ppm_ctx& c) {
         }
     c.tB_begin.push_back((int)c.bricks.size());
   }
+  c.brick_fill = zones / slots;
+  c.brick_zones = zones / count;
 }
 
 

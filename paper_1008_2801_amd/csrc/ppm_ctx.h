@@ -45,6 +45,7 @@ struct ppm_ctx {
   std::vector<int> tY_begin, tZ_begin;  // nbox + 1
   std::vector<Brick> bricks;
   std::vector<int> tB_begin;            // nbox + 1
+  double brick_fill = 1.0, brick_zones = 0.0;  // of bricks of BRICK_E (DevLevel)
   int fused = FINAL_RULE;               // form of the final stage
   int stream_e[3] = {16, 8, 32};        // tile extents of the streamed final stage
   // front end: 0 trace and stage-1 solves as two staged kernels; 1 one
@@ -136,6 +137,8 @@ struct ppm_ctx {
     for (int f = 0; f < 6; ++f) L.inflow.p[f] = inflow[f];
     for (int d = 0; d < 3; ++d) L.inflow.ext[d] = layout.domain.hi[d] - layout.domain.lo[d] + 1;
     L.bricks = d_bricks;
+    L.brick_fill = brick_fill;
+    L.brick_zones = brick_zones;
     L.fused = fused;
     for (int d = 0; d < 3; ++d) L.stream_e[d] = stream_e[d];
     L.fbricks = d_fbricks;

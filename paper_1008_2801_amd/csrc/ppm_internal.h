@@ -204,6 +204,8 @@ struct DevLevel {
   int tile;            // zones per tile of the tile lists (threads per workgroup)
   InflowView inflow;
   const Brick* bricks;  // valid-zone blocks of every box (fused final stage)
+  double brick_fill;    // mean share of a brick row's x slots that hold zones (at most a box's extent)
+  double brick_zones;   // mean valid zones of a brick of BRICK_E
   int fused;            // FINAL_*: the final stage's form
   int stream_e[3];      // form 2: x, y extents of a tile (threads = product) and the z run
   const Brick* fbricks; // traced-grid x-y tiles with z runs (streamed front end)

@@ -1056,15 +1056,27 @@ bool final_columns_pay(long long LE, long long zones, int groups) {
 }
 
 // Whether the final stage runs in bricks where it does not run in columns: from
-// two workgroups per CU on, and in FP32 (half the planes, so less to save, and
-// bricks cut to a box's extent leave lanes unused) on boxes below 80^3 zones.
-// Step staged -> bricks (us): FP64 64^3 136 -> 131, 64 boxes of 16^3 187 -> 170,
-// 256 x 256 x 4 179 -> 165, 96^3 449 -> 425, 8 boxes of 64^3 1158 -> 1067, 160^3
-// 2008 -> 1914; with fewer bricks 48^3 (288) 78 -> 86, 100 x 50 x 30 (416) 94.5
-// -> 97.4.  FP32 64 boxes of 32^3 764 -> 708, 64 of 64^3 5600 -> 5372; but one
-// box of 112^3 417 -> 435, of 256^3 4804 -> 4853.
-template <class S> bool final_bricks_pay(long long zones, int bricks) {
-  return bricks >= 512 && (sizeof(S) == 8 || zones < 512000);
+// two workgroups per CU on, unless the boxes' extents cut thin bricks, whose
+// lanes idle and whose faces are solved twice: rows a few zones longer than
+// whole bricks (brick_fill) and boxes a few zones wide (brick_zones).  FP32 has
+// half the planes to save, so it needs fuller bricks, the more so where fewer
+// than four rounds of workgroups leave the last one part empty.
+// Step staged -> bricks (us).  FP64: 64^3 136 -> 131, 64 boxes of 16^3 187 -> 170,
+// 256 x 256 x 4 179 -> 165, 8 boxes of 64^3 1158 -> 1067, 125 boxes of 36^3 (fill
+// 0.56) 3404 -> 3349, 7^3 (86 zones) 1888 -> 1852; but 48^3 (288 bricks) 78 -> 86,
+// 27 boxes of 35^3 (0.55) 715 -> 735, 64 of 33^3 (0.52) 1439 -> 1501, 4 x 256 x 256
+// (64 zones) 214 -> 243, 4096 boxes of 6^3 (54) 1123 -> 1231.  FP32: 64 boxes of
+// 64^3 5600 -> 5372, 27 of 48^3 (0.75) 1022 -> 1004, 8 of 72^3 (0.75, 7776
+// bricks) 977 -> 970, 512 boxes of 8^3 (128 zones) 175.5 -> 174; but 72^3 (972
+// bricks) 133 -> 137, 68^3 (0.71) 116 -> 123, 27 of 45^3 (0.70) 851 -> 870, 125 of
+// 36^3 2187 -> 2207, 64 of 33^3 853 -> 922, 4 x 256 x 256 141 -> 186, 7^3 1058 ->
+// 1108.  On larger boxes FP32 gains and loses with the extents: 128^3, 160^3 and 8
+// boxes of 128^3 (5228 -> 5048) gain 0.5 to 4%, 112^3 417 -> 435 and 256^3 4804 ->
+// 4853 lose; they are left staged.
+template <class S> bool final_bricks_pay(const DevLevel& L, int bricks) {
+  if (bricks < 512) return false;
+  if (sizeof(S) == 8) return L.brick_fill >= 0.55 && L.brick_zones >= 80.0;
+  return L.LE / L.nbox < 512000 && L.brick_fill >= (bricks < 2048 ? 0.95 : 0.75) && L.brick_zones >= 112.0;
 }
 
 // The form that the final stage of a launch of nB bricks or nCol columns takes.
@@ -1073,7 +1085,7 @@ template <class S> int final_form(const DevLevel& L, int nB, int nCol) {
   if (L.fused == FINAL_COLUMNS) return sizeof(S) == 8 ? FINAL_COLUMNS : FINAL_STAGED;
   if (L.fused != FINAL_RULE) return L.fused;
   if (sizeof(S) == 8 && final_columns_pay(L.LE, zones, nCol)) return FINAL_COLUMNS;
-  return final_bricks_pay<S>(zones, nB) ? FINAL_BRICKS : FINAL_STAGED;
+  return final_bricks_pay<S>(L, nB) ? FINAL_BRICKS : FINAL_STAGED;
 }
 
 template <class S>

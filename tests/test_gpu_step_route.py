@@ -23,6 +23,14 @@ CASES = [
     (([126], [126], [254]), 1, (3, 0)), (([125], [126], [254]), 1, (2, 0)),
     # bricks from 512 of them on
     (([64], [64], [64]), 0, (2, 1)), (([64], [64], [60]), 0, (2, 0)), (([64], [64], [64]), 1, (2, 1)),
+    # not where the boxes' extents cut thin ones: rows of 33 (shares of a brick
+    # row filled 0.52), 36 (0.56) and 48 zones (0.75), boxes 4, 5, 7 and 8 wide
+    (([33] * 4, [33] * 4, [33] * 4), 0, (3, 0)), (([33] * 4, [33] * 4, [33] * 4), 1, (2, 0)),
+    (([36] * 4, [36] * 2, [36] * 2), 0, (2, 1)), (([36] * 4, [36] * 2, [36] * 2), 1, (2, 0)),
+    (([48] * 3, [48] * 2, [48] * 2), 1, (2, 1)), (([72], [72], [72]), 1, (2, 0)),
+    (([4], [256], [256]), 0, (2, 0)), (([4], [256], [256]), 1, (2, 0)),
+    (([5] * 8, [5] * 8, [5] * 8), 0, (2, 0)), (([7] * 8, [7] * 8, [7] * 8), 0, (2, 1)),
+    (([7] * 8, [7] * 8, [7] * 8), 1, (2, 0)), (([8] * 8, [8] * 8, [8] * 8), 1, (2, 1)),
     # columns from 1536 workgroups on, on boxes of a million zones and more on
     # average: 131 x 12 workgroups here, 49 x 5 a box of the eight
     (([200], [160], [180]), 0, (3, 4)), (([200], [60], [70] * 8), 0, (3, 1)),
