@@ -128,6 +128,7 @@ struct ppm_ctx {
     L.desc_start = d_start;
     L.consts = d_consts;
     L.nbox = layout.nbox;
+    L.layer0 = (long long)(boxes[0].hi[0] - boxes[0].lo[0] + 3) * (boxes[0].hi[1] - boxes[0].lo[1] + 3);
     L.flags = d_flags;
     L.inv_start = d_inv_start;
     L.inv_idx = d_inv_idx;

@@ -140,18 +140,23 @@ struct StepConsts {
 
 // The largest speed of the update's workgroups by index modulo the slots (the
 // bits of non-negative doubles).  They belong to a step, not to its context,
-// so that steps in flight on two streams do not meet in them: each lies at the
-// start of one of the workspace's final-flux planes, in the first box's layer
-// z = -1 (nine zones at least), which holds no face of a valid zone and so is
-// read and written by no stage.  first: the first such plane, plane: its bytes.
-constexpr int SPEED_SLOTS = 15;
+// so that steps in flight on two streams do not meet in them: they lie in the
+// step's workspace, in the first box's layer z = -1 of the first final-flux
+// plane (nine zones at least), which holds no face of a valid zone and so is
+// read and written by no stage.  A cache line each where the layer is long
+// enough, else closer together, on the smallest boxes all in one place; one
+// plane each took 0.4 us a step more on small levels.
+constexpr int SPEED_SLOTS = 16;
 struct SpeedSlots {
   char* first;
-  long long plane;
-  __host__ __device__ unsigned long long* at(int k) const {
-    return (unsigned long long*)(((size_t)(first + k * plane) + 7) & ~(size_t)7);
-  }
+  int stride;
+  __host__ __device__ unsigned long long* at(int k) const { return (unsigned long long*)(first + k * stride); }
 };
+// layer: the start and bytes of that layer.
+inline SpeedSlots speed_slots(char* layer, long long bytes) {
+  const long long gap = (bytes - 16) / SPEED_SLOTS / 8 * 8;  // the first slot is aligned up to 8 bytes
+  return SpeedSlots{(char*)(((size_t)layer + 7) & ~(size_t)7), (int)(gap < 128 ? gap : 128)};
+}
 
 // Number of planes in the traced-grid (E) arena: flattening 1, traces 30,
 // stage-1 fluxes 15, stage-2 fluxes 30, final fluxes 15.
@@ -187,6 +192,7 @@ enum { FRONT_STAGED = 0, FRONT_STREAM = 1, FRONT_X = 2, FRONT_COLUMNS = 3, FRONT
 struct DevLevel {
   const DevBox* boxes;
   int nbox;
+  long long layer0;    // zones of the first box's traced grid in one z layer
   const Tile* tilesS;  // tiles over the stored grids
   const Tile* tilesE;  // tiles over the traced grids
   const Tile* tilesX;  // runs of XF_OWNED traced zones (front forms 2, 3)

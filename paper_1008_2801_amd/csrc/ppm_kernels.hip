@@ -753,8 +753,9 @@ __device__ __forceinline__ void riemann2_body(int tt, const Tile* __restrict__ t
 // The three axes of a tile are consecutive workgroups of one XCD: every
 // stage-1 flux is read by two of them, and the second read then comes from
 // the caches instead of HBM (grid rows per axis read it again a whole pass
-// over the level later): 256^3 FP64 2.46 -> 2.31 ms, 216 boxes of 64^3 9.22
-// -> 8.78 ms.  (The traces, which share the primitives the same way, are
+// over the level later): 256^3 FP64 2.46 -> 2.31 ms, FP32 1.62 -> 1.59, 216
+// boxes of 64^3 9.22 -> 8.78 ms, 512 boxes of 64^3 FP32 14.1 -> 13.9; of the
+// sizes tried only 80^3 FP64 loses, 73 -> 78 us.  (The traces, which share the primitives the same way, are
 // slower like this, 1.26 -> 1.46 ms: their stencils along z then find less
 // of the previous planes in L2.)
 template <class S>
@@ -906,7 +907,7 @@ __device__ __forceinline__ double fold_signal_speed(double s, double r, double m
 // already as large, and a minimum only from those that raised it (one from each
 // costs a 256 x 256 x 4 step 7 us).  On a level that the chip holds at once all
 // workgroups come here together, before any has raised the maximum, and queue
-// at its address: slots (the workgroups by index) each let only
+// at its address: slots (the workgroups by index, and so by XCD) each let only
 // the workgroups pass that raise the slot's own maximum (256 x 256 x 4: k_update
 // 25.1 -> 14.5 us, 64^3: 19.6 -> 12.8).  Every lane of the workgroup must call it.
 __device__ __forceinline__ void block_speed_to(double s, double* dt, double cfl,
@@ -1562,7 +1563,7 @@ hipError_t step_impl(const DevLevel& L, int tS0, int tS1, int tE0, int tE1, int 
                      hipEvent_t* ev, int upto, SpeedOut so, StepStart st) {
   S* prim = (S*)work;
   S* ework = prim + P_PLANES * L.LS;
-  so.slots = st.slots = SpeedSlots{(char*)(ework + E_F3 * L.LE), (long long)sizeof(S) * L.LE};
+  so.slots = st.slots = speed_slots((char*)(ework + E_F3 * L.LE), L.layer0 * (long long)sizeof(S));
   const int nS = tS1 - tS0, nE = tE1 - tE0;
   const Tile* TS = L.tilesS + tS0;
   const Tile* TE = L.tilesE + tE0;
