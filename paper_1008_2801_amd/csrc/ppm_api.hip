@@ -1378,11 +1378,16 @@ int ppm_autotune(ppm_ctx* ctx, const double* U, double* Unew, const double dx[3]
         for (int d = 0; d < 3; ++d) bfe[d] = sh[d];
       }
     }
-    for (int f = 2; f <= 3 && !rc; ++f)
-      if (!(rc = ppm_set_front_form(ctx, f)) && !(rc = timed(ms)) && ms < best) {
+    for (int f = 2; f <= 3 && !rc; ++f) {
+      // form 3 only where it is not what form 2 takes by size: a batched step's
+      // times cannot tell them apart, but form 3 holds for single boxes too
+      int32_t front = 0, last = 0;
+      if (f == 3 && !(rc = ppm_get_step_route(ctx, params->precision, &front, &last)) && front == FRONT_COLUMNS) break;
+      if (!rc && !(rc = ppm_set_front_form(ctx, f)) && !(rc = timed(ms)) && ms < best) {
         best = ms;
         bfront = f;
       }
+    }
     if (!rc) rc = ppm_set_front_form(ctx, 0);
   }
   (void)hipEventDestroy(e0);

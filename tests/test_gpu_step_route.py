@@ -84,3 +84,25 @@ def test_one_launch_front_end_needs_its_tile_size():
     with pytest.raises(P.PPMError, match="step_route"):
         lev.get_step_route(2)
     lev.close()
+
+
+def test_autotuner_leaves_the_front_end_by_size_where_it_takes_columns():
+    """Form 3 (columns always) is the same batched step there, but holds for the
+    launches of single small boxes as well."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lay = I.tensor_tiling([64] * 2, [64] * 2, [64] * 3)
+    lev = P.Level(lay)
+    p = P.params(gamma=1.4)
+    assert lev.get_step_route()[0] == 3
+    U = lev.new_state()
+    for b in range(lay.nbox):
+        o, n = int(lev.offsets[b]), lay.box_size(b)
+        v = U[o:o + n].view(5, -1)
+        v.fill_(0.1)
+        v[0] = 1.0
+        v[4] = 2.5
+    for _ in range(3):
+        lev.autotune(U, (0.1, 0.1, 0.1), p, reps=1)
+        assert lev.get_front_form() != 3
+    lev.close()
