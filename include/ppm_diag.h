@@ -2,11 +2,14 @@
  * ppm_diag.h -- C ABI of the arithmetic diagnostics of the PPM step's
  * kernels (libppm_diag.so, a library of its own beside libppm.so).
  *
- * The step's Riemann solver (the two-shock solver of the compressible
- * code's explicit advance, paper Sec. 1), its corrected states, tracing and
- * flattening divide and take square roots with the core of the compiler's
- * correctly rounded sequences, without the operand scaling that their
- * magnitudes never need.  These entry points run exactly those sequences on
+ * Parts of the step (the FP32 two-shock solver of the compressible code's
+ * explicit advance, paper Sec. 1, the star state's sound speed and the fan's
+ * weight in FP64, a quotient of the tracing, the flattening's pressure ratio)
+ * divide and take square roots with the core of the compiler's correctly
+ * rounded sequences, without the operand scaling that their magnitudes never
+ * need.  (The FP64 solver's other quotients and roots come from refined
+ * reciprocals and reciprocal roots, which are not evaluated here.)  These entry
+ * points run exactly those sequences on
  * the device for caller-given arguments, so that a caller (the test suite)
  * can compare them with IEEE results on the host; likewise the integer
  * division the kernels decode zone indices with.  They are not part of the
@@ -26,13 +29,12 @@
 extern "C" {
 #endif
 
-/* out[i] = one of the FP64 square roots the Riemann solver takes, for n
- * arguments x[i].  form 0: the root of the wave-speed factor
- * 1 + beta (p/p_s - 1) (>= 1 - beta > 0; the Lagrangian shock speed of
- * Colella-Glaz 1985 is C_s times it); form 1: the root of gamma p rho (the
- * Lagrangian sound speed C_s) and of the star state's gamma p / rho; form 2:
- * the FP32 root of the wave-speed factor, taken of (float) x[i] and returned
- * widened to double.  The IEEE root for every finite argument >= 2^-767
+/* out[i] = one of the square roots of the Riemann solver's kind, for n
+ * arguments x[i].  form 0: the core that form 1 completes; form 1: the FP64
+ * root of the star state's gamma p / rho; form 2: the FP32 root of the
+ * wave-speed factor 1 + beta (p/p_s - 1) (>= 1 - beta > 0; the Lagrangian shock
+ * speed of Colella-Glaz 1985 is C_s times it), taken of (float) x[i] and
+ * returned widened to double.  The IEEE root for every finite argument >= 2^-767
  * (form 2: >= 2^-96; form 1: also for 0, +inf, negative and NaN
  * arguments).  Invalid: n < 0, null pointers with n > 0, another form. */
 int ppm_diag_sqrt_values(const double* x, double* out, int64_t n, int32_t form, void* stream);
