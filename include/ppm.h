@@ -408,7 +408,8 @@ int ppm_get_stream_tiling(const ppm_ctx* ctx, int32_t* sx, int32_t* sy, int32_t*
  * each trace 64 consecutive zones, the first of them the previous
  * wavefront's last, so both states of every x face they solve meet in
  * neighbouring lanes (a lane shuffle; no LDS, no barrier); y and z as in
- * form 3 on levels large enough for it to pay, else staged (the default).
+ * form 3 on levels large enough for it to pay, else staged; on small levels
+ * of 256-zone tiles all axes in one launch (the default).
  * form 3: every axis fused; along y and z each lane walks a column of traced
  * zones along the axis with the reconstruction's stencil in registers and
  * solves each zone's low face from the state carried from the zone below.

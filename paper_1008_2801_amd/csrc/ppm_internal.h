@@ -217,7 +217,8 @@ struct DevLevel {
   const Brick* fbricks; // traced-grid x-y tiles with z runs (streamed front end)
   int front;            // 1: trace + stage-1 solves in one kernel streamed along z (k_front_stream);
                         // 2: the x axis's trace + stage-1 solves in one kernel (k_front_x), y's and z's
-                        // in columns where that pays (k_front_yz); 3: in columns always
+                        // in columns where that pays (k_front_yz), all in one launch on small levels
+                        // (k_front_small); 3: in columns always
   int front_m[2];       // largest x, y extents of the front tiles (LDS layout, lanes)
 };
 

@@ -434,7 +434,8 @@ class Level:
     def set_front_form(self, form):
         """0: trace and stage-1 solves as two staged kernels; 1: one kernel
         streamed along z; 2: the x axis fused, y and z too on large
-        levels; 3: every axis fused (ppm_set_front_form)."""
+        levels, one launch for all on small ones; 3: every axis fused
+        (ppm_set_front_form)."""
         self._check(lib().ppm_set_front_form(self.ctx, int(form)), "ppm_set_front_form")
 
     def get_front_form(self):
